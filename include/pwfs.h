@@ -55,7 +55,13 @@ typedef enum {
   PWFS_ESTATE = -5         /* call out of order (e.g. frames > max)     */
 } pwfs_status;
 
-/* Arithmetic of the two transforms of the forward model. */
+/*
+ * Arithmetic of the two transforms of the forward model.  Sensors of the image
+ * windows alone (no PWFS_F_FULL_PLANE, no field stop) with n_pupil <= 256 run
+ * FP32 and the split precisions as one real Toeplitz product per axis on the
+ * matrix cores, with scaled fp16 hi/lo operands and fp32 sums (1.7e-7 of the
+ * intensity; the float32 FFTs: 2.5e-7).  All else runs as named here.
+ */
 typedef enum {
   PWFS_FP32 = 0,    /* radix FFTs in float32 on the vector ALUs            */
   PWFS_BF16 = 1,    /* dense DFT operator as bf16 MFMA products, 1 term     */
@@ -189,7 +195,8 @@ int pwfs_slopes(pwfs_plan_t plan, const float* d_intensity, int n_frames, float*
  * Execution tuning of a plan (chosen by the autotuner, see autotune.py).
  *  mode       PWFS_MODE_LAUNCHES: per sensor, a field, a row and a column
  *             launch per pass; PWFS_MODE_PERSISTENT: one persistent launch per
- *             pass for all sensors, whose workgroups claim field, row and
+ *             pass for all Toeplitz sensors and one for all FFT ones, whose
+ *             workgroups claim field, row and
  *             column work items from a device counter (a sensor's row items
  *             wait for its field items, its column items for its row items).
  *             Both modes give bit-identical results.  PWFS_MODE_FUSED (FP32

@@ -30,6 +30,7 @@ namespace pwfs {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));   // 16 bytes, 8 x 16-bit
 
 constexpr int kGemmTile = 128;  // BM = BN

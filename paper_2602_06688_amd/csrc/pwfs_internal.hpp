@@ -9,11 +9,13 @@
 
 #include "pwfs.h"
 
+struct pwfs_plan_s;
+
 namespace pwfs {
 
 // per-sensor workspace regions, in order
 enum Region {
-  R_AMP = 0, R_RX, R_RY, R_AK, R_MROW, R_MCOL, R_TW, R_VALID, R_REF, R_REFINT, R_ZERO, R_MFMA,
+  R_AMP = 0, R_RX, R_RY, R_AK, R_MROW, R_MCOL, R_TW, R_VALID, R_REF, R_REFINT, R_ZERO, R_MFMA, R_TOEP,
   kRegions
 };
 
@@ -40,6 +42,7 @@ struct SensorPlan {
   size_t opd_offset, int_offset, slope_offset;
   float2* rbuf = nullptr;   // this sensor's pass scratch
   int row_tile = 0;         // row-pass tile rows (0: the default of its N)
+  bool toep = false;        // runs the Toeplitz passes (toep_eligible)
 };
 
 struct Layout {
@@ -72,6 +75,19 @@ int upload_mfma_tables(const pwfs_sensor_desc& d, char* dst, hipStream_t st, std
 struct Prof;
 int forward_mfma(const SensorPlan& sp, const float* opd, long long opd_stride, float* out, long long out_stride,
                  int nf, void* scratch, hipStream_t st, Prof* prof);
+
+// Toeplitz form on the matrix cores (pwfs_toep.hip)
+bool toep_eligible(const pwfs_sensor_desc& d);
+size_t toep_table_bytes(const pwfs_sensor_desc& d);
+size_t toep_scratch_frame_bytes(const pwfs_sensor_desc& d);
+size_t toep_scratch_bytes(const pwfs_sensor_desc& d, int chunk);
+int toep_frames_per_pass(const pwfs_sensor_desc& d);
+int upload_toep_tables(const pwfs_sensor_desc& d, char* dst, hipStream_t st, std::vector<std::vector<char>>& keep);
+void toep_prepare();
+int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, float* out, long long out_stride,
+                 int nf, float2* rbuf, hipStream_t st, Prof* prof);
+int forward_toep_hetero(pwfs_plan_s* p, const std::vector<int>& which, const float* opd, int f0, int nf, float* out,
+                        int* counters, int* flag, hipStream_t st);
 
 // Optional per-kernel timing: HIP events recorded on the launch stream
 // around each kernel (pool created when profiling is switched on).

@@ -17,6 +17,7 @@
 #include "pwfs.h"
 #include "pwfs_kernels.hpp"
 #include "pwfs_internal.hpp"
+#include "toep_hetero.hpp"
 
 namespace {
 
@@ -241,29 +242,39 @@ Geometry arm_geometry(const pwfs_sensor_desc& d, int arm) {
   return g;
 }
 
+// Tables of the FFT passes: every sensor that the Toeplitz form does not take,
+// the double roof's flat axes, and the sizes of the fused pass.
+static bool needs_fft_tables(const pwfs_sensor_desc& d) {
+  return !toep_eligible(d) || sensor_arms(d) == 2 || geometry(d).N <= 128;
+}
+
 // bytes of each per-sensor region, in workspace order
 static void sensor_regions(const pwfs_sensor_desc& d, size_t out[kRegions]) {
   const Geometry g = geometry(d);
   const bool ref = d.flags & PWFS_F_REF_SLOPES;
   out[R_AMP] = sizeof(float) * g.D * g.D;
-  out[R_RX] = sizeof(float2) * g.n_lam * g.n_a * g.D;
-  out[R_RY] = sizeof(float2) * g.n_lam * g.n_mod * g.D;
+  const bool fft = needs_fft_tables(d);
+  out[R_RX] = fft ? sizeof(float2) * g.n_lam * g.n_a * g.D : 0;
+  out[R_RY] = fft ? sizeof(float2) * g.n_lam * g.n_mod * g.D : 0;
   out[R_AK] = sizeof(int) * 2 * g.n_mod;
   const int arms = sensor_arms(d);
-  out[R_MROW] = sizeof(float2) * arms * g.n_lam * g.N;
-  out[R_MCOL] = sizeof(float2) * arms * g.n_lam * g.N;
-  out[R_TW] = sizeof(float2) * g.N;
+  out[R_MROW] = fft ? sizeof(float2) * arms * g.n_lam * g.N : 0;
+  out[R_MCOL] = fft ? sizeof(float2) * arms * g.n_lam * g.N : 0;
+  out[R_TW] = fft ? sizeof(float2) * g.N : 0;
   out[R_VALID] = (size_t)g.n * g.n;
   out[R_REF] = sizeof(float) * 2 * g.n * g.n;
   out[R_REFINT] = ref ? sizeof(float) * arms * g.N * g.N : 0;
   out[R_ZERO] = ref ? sizeof(float) * g.D * g.D : 0;
-  out[R_MFMA] = mfma_table_bytes(d);
+  const bool toep = toep_eligible(d);
+  out[R_MFMA] = toep ? 0 : mfma_table_bytes(d);
+  out[R_TOEP] = toep_table_bytes(d);
 }
 
 // per frame: the row-pass output [n_lam][n_a][Nc][Dp], then the pupil field
 // [n_lam][D][D] (the field block of a pass sits after all frames' R blocks)
 size_t rbuf_frame_bytes(const pwfs_sensor_desc& d) {
   const Geometry g = geometry(d);
+  if (toep_eligible(d)) return toep_scratch_frame_bytes(d);
   if (d.precision != PWFS_FP32) return mfma_scratch_frame_bytes(d);
   return sizeof(float2) * ((size_t)g.n_lam * g.n_a * g.Nc * g.Dp + (size_t)g.n_lam * g.D * g.D);
 }
@@ -275,15 +286,17 @@ size_t rbuf_field_offset(const pwfs_sensor_desc& d, int nf) {
 }
 
 int choose_chunk(const pwfs_sensor_desc* s, int n, int max_frames) {
-  // enough frames per pass that the column pass launches >= ~16384 workgroups
-  // (16 rounds of the chip's resident workgroups, so a launch's tail is a
-  // small part of it), with the scratch of one pass (all sensors) capped at
-  // 12 GiB (of the 288 GB of HBM)
+  // enough frames per pass that a launch's tail is a small part of it: >= ~16384
+  // workgroups of the FFT or matrix-core column pass (16 rounds of the chip's
+  // resident workgroups) or four rounds of the Toeplitz column pass, which
+  // comes to about the same frames; the scratch of one pass (all sensors) is
+  // capped at 12 GiB (of the 288 GB of HBM)
   size_t per = 0;
   int want = 1;
   for (int i = 0; i < n; ++i) {
     const Geometry g = geometry(s[i]);
     per += rbuf_frame_bytes(s[i]);
+    if (toep_eligible(s[i])) want = std::max(want, toep_frames_per_pass(s[i]));
     int colwg;
     if (s[i].precision == PWFS_FP32) {
       const int G = kBlock / fft_lanes(g.N);
@@ -297,6 +310,12 @@ int choose_chunk(const pwfs_sensor_desc* s, int n, int max_frames) {
   int c = std::min(want, max_frames);
   if (per > 0) c = (int)std::min<size_t>((size_t)c, std::max<size_t>(1, cap / per));
   return std::max(1, c);
+}
+
+// frames per pass of a new plan: passes of equal size
+int equal_chunk(int max_chunk, int max_frames) {
+  const int passes = (max_frames + max_chunk - 1) / max_chunk;
+  return (max_frames + passes - 1) / passes;
 }
 
 int fft_r0(int N) {
@@ -324,21 +343,33 @@ int fft_lanes(int N) {
 int layout(const pwfs_sensor_desc* s, int n, int max_frames, Layout* L) {
   size_t off = 0;
   L->offsets.assign((size_t)n * kRegions, 0);
+  L->chunk = choose_chunk(s, n, max_frames);
+  // a Toeplitz sensor's reference intensity is needed while its plan is built
+  // only: it sits behind one frame's scratch where a pass has more frames
+  std::vector<size_t> one(n, 0);
   for (int i = 0; i < n; ++i) {
     size_t sz[kRegions];
     sensor_regions(s[i], sz);
+    if (toep_eligible(s[i])) {
+      one[i] = align256(toep_scratch_bytes(s[i], 1));
+      if (toep_scratch_bytes(s[i], L->chunk) >= one[i] + sz[R_REFINT])
+        sz[R_REFINT] = 0;
+      else
+        one[i] = 0;
+    }
     for (int r = 0; r < kRegions; ++r) {
       L->offsets[(size_t)i * kRegions + r] = off;
       off += align256(sz[r]);
     }
   }
-  L->chunk = choose_chunk(s, n, max_frames);
   // one scratch region per sensor (sensors of a persistent pass run together)
   L->rbuf_offset = off;
   L->sensor_rbuf.assign(n, 0);
   for (int i = 0; i < n; ++i) {
     L->sensor_rbuf[i] = off;
-    off += align256(rbuf_frame_bytes(s[i]) * (size_t)L->chunk);
+    if (one[i]) L->offsets[(size_t)i * kRegions + R_REFINT] = off + one[i];
+    off += align256(toep_eligible(s[i]) ? toep_scratch_bytes(s[i], L->chunk)
+                                        : rbuf_frame_bytes(s[i]) * (size_t)L->chunk);
   }
   L->counters_offset = off;
   off += align256(sizeof(int) * 64);
@@ -393,8 +424,9 @@ int upload_tables(const pwfs_sensor_desc& d, char* ws, const size_t* off, hipStr
   std::vector<TiltPoint> pts;
   std::vector<double> key_tx;
   tilt_points(d, pts, key_tx);
-  std::vector<float> rx(2 * (size_t)g.n_lam * g.n_a * g.D), ry(2 * (size_t)g.n_lam * g.n_mod * g.D);
-  for (int l = 0; l < g.n_lam; ++l) {
+  const bool fft = needs_fft_tables(d);
+  std::vector<float> rx(fft ? 2 * (size_t)g.n_lam * g.n_a * g.D : 0), ry(fft ? 2 * (size_t)g.n_lam * g.n_mod * g.D : 0);
+  for (int l = 0; fft && l < g.n_lam; ++l) {
     const double sc = d.lambda_ref_nm / d.lambda_nm[l];   // tilts are given at lambda_ref
     for (int a = 0; a < g.n_a; ++a) {
       for (int x = 0; x < g.D; ++x) {
@@ -421,9 +453,9 @@ int upload_tables(const pwfs_sensor_desc& d, char* ws, const size_t* off, hipStr
   // (the field stop, a fixed sky angle, is narrower in samples at longer
   // wavelengths, so both tables are per wavelength)
   const int arms = sensor_arms(d);
-  std::vector<float> mrow(2 * (size_t)arms * g.n_lam * g.N), mcol(2 * (size_t)arms * g.n_lam * g.N);
-  std::vector<float> tw(2 * (size_t)g.N);
-  for (int a = 0; a < arms; ++a) {
+  std::vector<float> mrow(fft ? 2 * (size_t)arms * g.n_lam * g.N : 0), mcol(mrow.size());
+  std::vector<float> tw(fft ? 2 * (size_t)g.N : 0);
+  for (int a = 0; fft && a < arms; ++a) {
     const Geometry ga = arms == 2 ? arm_geometry(d, a) : g;
     const double share = arms == 2 ? 0.5 : 1.0;
     for (int l = 0; l < g.n_lam; ++l) {
@@ -436,7 +468,7 @@ int upload_tables(const pwfs_sensor_desc& d, char* ws, const size_t* off, hipStr
       for (size_t i = 0; i < mc.size(); ++i) mcol[at + i] = (float)mc[i];
     }
   }
-  for (int i = 0; i < g.N; ++i) put_c(tw, i, cis(-2.0 * kPi * i / g.N));
+  for (int i = 0; fft && i < g.N; ++i) put_c(tw, i, cis(-2.0 * kPi * i / g.N));
   auto up = [&](int region, const void* src, size_t bytes) -> int {
     if (!bytes) return PWFS_OK;
     keep.emplace_back((const char*)src, (const char*)src + bytes);
@@ -456,7 +488,9 @@ int upload_tables(const pwfs_sensor_desc& d, char* ws, const size_t* off, hipStr
   if (d.flags & PWFS_F_REF_SLOPES) {
     HIP_TRY(hipMemsetAsync(ws + off[R_ZERO], 0, sizeof(float) * g.D * g.D, st), "hipMemsetAsync(zero)");
   }
-  if (d.precision != PWFS_FP32) {
+  if (toep_eligible(d)) {
+    if ((rc = upload_toep_tables(d, ws + off[R_TOEP], st, keep))) return rc;
+  } else if (d.precision != PWFS_FP32) {
     if ((rc = upload_mfma_tables(d, ws + off[R_MFMA], st, keep, sumA2))) return rc;
   }
   return PWFS_OK;
@@ -738,14 +772,33 @@ bool hetero_eligible(const SensorPlan& sp) {
   return sp.desc.precision == PWFS_FP32 && sp.g.qmax <= 3 && sp.g.N >= 256 && sp.arms == 1;
 }
 
+// One persistent launch per pass for the sensors of each form (Toeplitz, FFT).
+// The Toeplitz launch's counters sit behind the FFT one's; the error flag is
+// shared.
+constexpr int kToepCounters = 32;
+static_assert(kHeteroFlag < kToepCounters, "the two launches' counters are apart");
+
 int forward_hetero(pwfs_plan_s* p, const float* opd, int f0, int nf, float* out, hipStream_t st) {
   HeteroArgs ha{};
-  const int ns = (int)p->s.size();
-  if (ns > kMaxHetero) return fail(PWFS_EUNSUPPORTED, "persistent mode takes at most %d sensors", kMaxHetero);
+  if ((int)p->s.size() > kMaxHetero)
+    return fail(PWFS_EUNSUPPORTED, "persistent mode takes at most %d sensors", kMaxHetero);
+  std::vector<int> fft, toep;
+  for (size_t i = 0; i < p->s.size(); ++i) (p->s[i].toep ? toep : fft).push_back((int)i);
+  // clears every counter but the sticky flag
+  hipLaunchKernelGGL(k_counter_reset, dim3(1), dim3(64), 0, st, p->counters, kHeteroFlag);
+  HIP_TRY(hipGetLastError(), "launch k_counter_reset");
+  if (!toep.empty()) {
+    hipLaunchKernelGGL(k_counter_reset, dim3(1), dim3(64), 0, st, p->counters + kToepCounters, kHeteroFlag);
+    HIP_TRY(hipGetLastError(), "launch k_counter_reset");
+    const int rc = forward_toep_hetero(p, toep, opd, f0, nf, out, p->counters + kToepCounters,
+                                       p->counters + kHeteroFlag, st);
+    if (rc || fft.empty()) return rc;
+  }
   size_t lds = 0;
   std::vector<std::pair<double, int>> cost;
+  const int ns = (int)fft.size();
   for (int i = 0; i < ns; ++i) {
-    const SensorPlan& sp = p->s[i];
+    const SensorPlan& sp = p->s[fft[i]];
     const PassArgs pa = build_pass_any(sp, opd + sp.opd_offset + (long long)f0 * p->opd_stride,
                                        (long long)p->opd_stride, out + sp.int_offset + (long long)f0 * p->int_stride,
                                        (long long)p->int_stride, nf, sp.rbuf, p->tune.row_groups);
@@ -769,8 +822,6 @@ int forward_hetero(pwfs_plan_s* p, const float* opd, int f0, int nf, float* out,
   ha.total = total;
   ha.counters = p->counters;
   ha.spin_limit = p->tune.spin_limit != 0 ? p->tune.spin_limit : (1 << 24);
-  hipLaunchKernelGGL(k_counter_reset, dim3(1), dim3(64), 0, st, p->counters, kHeteroFlag);
-  HIP_TRY(hipGetLastError(), "launch k_counter_reset");
   const int grid = p->n_cu * std::max(1, p->tune.wg_per_cu);
   const int slot = p->prof.begin(st);
   hipLaunchKernelGGL(k_hetero, dim3((unsigned)grid), dim3(kBlock), lds, st, ha);
@@ -856,6 +907,7 @@ int prepare_kernels() {
   lds_limit((const void*)k_slopes<1024, 2>);
   lds_limit((const void*)k_slopes<1024, 4>);
   lds_limit((const void*)k_slopes<1024, 8>);
+  toep_prepare();
   lds_limit((const void*)k_hetero);
   lds_limit((const void*)k_fused<64, 3>);
   lds_limit((const void*)k_fused<64, 4>);
@@ -993,10 +1045,10 @@ int pwfs_plan(const pwfs_sensor_desc* s, int n, int max_frames, void* ws, size_t
   pwfs_plan_s* p = new (std::nothrow) pwfs_plan_s();
   if (!p) return fail(PWFS_EINVAL, "out of host memory");
   p->max_frames = max_frames;
-  p->chunk = L.chunk;
+  p->chunk = equal_chunk(L.chunk, max_frames);
   p->max_chunk = L.chunk;
   p->tune.mode = PWFS_MODE_LAUNCHES;
-  p->tune.chunk = L.chunk;
+  p->tune.chunk = p->chunk;
   p->tune.wg_per_cu = 2;
   p->tune.row_groups = 2048;
   p->tune.max_chunk = L.chunk;
@@ -1017,6 +1069,7 @@ int pwfs_plan(const pwfs_sensor_desc* s, int n, int max_frames, void* ws, size_t
     sp.desc = s[i];
     sp.g = geometry(s[i]);
     sp.arms = sensor_arms(s[i]);
+    sp.toep = toep_eligible(s[i]);
     for (int a = 0; a < sp.arms; ++a) sp.arm_g[a] = arm_geometry(s[i], a);
     for (int r = 0; r < kRegions; ++r) sp.dev[r] = (char*)ws + L.offsets[(size_t)i * kRegions + r];
     sp.rbuf = (float2*)((char*)ws + L.sensor_rbuf[i]);
@@ -1289,13 +1342,16 @@ int forward_sensor(pwfs_plan_s* p, int i, const float* opd, long long opd_stride
         arm.ident = sp.desc.fov_lod > 0.0 ? 0 : (a == 0 ? 1 : 2);
         arm.dev[R_MROW] = (char*)sp.dev[R_MROW] + sizeof(float2) * (size_t)a * sp.g.n_lam * sp.g.N;
         arm.dev[R_MCOL] = (char*)sp.dev[R_MCOL] + sizeof(float2) * (size_t)a * sp.g.n_lam * sp.g.N;
-        rc = forward_fp32(arm, o, opd_stride, r + (size_t)a * sp.g.N * sp.g.N, out_stride, n, sp.rbuf, st,
-                          &p->prof);
+        float* plane = r + (size_t)a * sp.g.N * sp.g.N;
+        rc = sp.toep ? forward_toep(arm, o, opd_stride, plane, out_stride, n, sp.rbuf, st, &p->prof)
+                     : forward_fp32(arm, o, opd_stride, plane, out_stride, n, sp.rbuf, st, &p->prof);
         if (rc) return rc;
       }
       continue;
     }
-    if (sp.desc.precision == PWFS_FP32)
+    if (sp.toep)
+      rc = forward_toep(sp, o, opd_stride, r, out_stride, n, sp.rbuf, st, &p->prof);
+    else if (sp.desc.precision == PWFS_FP32)
       rc = forward_fp32(sp, o, opd_stride, r, out_stride, n, sp.rbuf, st, &p->prof);
     else
       rc = forward_mfma(sp, o, opd_stride, r, out_stride, n, sp.rbuf, st, &p->prof);

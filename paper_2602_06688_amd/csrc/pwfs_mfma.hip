@@ -644,3 +644,5 @@ int forward_mfma(const SensorPlan& sp, const float* opd, long long os, float* ou
 }
 
 }  // namespace pwfs
+
+#include "toep_forward.hpp"

@@ -1,0 +1,578 @@
+// toep_forward.hpp -- kernels and host side of the Toeplitz form of the
+// forward model (toep_device.hpp): which sensors take it, its tables and
+// scratch, the pupil field in its layout, and its launches.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cmath>
+#include <complex>
+#include <cstdio>
+#include <cstring>
+#include <vector>
+
+#include "fft_device.hpp"
+#include "pwfs.h"
+#include "pwfs_geom.hpp"
+#include "pwfs_internal.hpp"
+#include "toep_field.hpp"
+
+namespace pwfs {
+namespace {
+
+constexpr double kPiT = 3.14159265358979323846264338327950288;
+size_t ta256(size_t x) { return (x + 255) & ~size_t(255); }
+
+struct ToepGeom {
+  int KS, Dh, Dq;
+};
+
+ToepGeom toep_geom(const pwfs_sensor_desc& d) {
+  ToepGeom t;
+  t.Dh = d.n_pupil / 2;
+  t.KS = (t.Dh + 15) / 16;
+  t.Dq = (t.Dh + 7) & ~7;
+  return t;
+}
+
+// ------------------------------------------------------------- kernels ----
+template <int KS>
+__global__ __launch_bounds__(kToepRowThreads, 2) void k_toep_rows(ToepRowArgs p) {
+  extern __shared__ __align__(16) unsigned char toep_smem[];
+  toep_rows_body<KS>(p, blockIdx.x, toep_smem, threadIdx.x);
+}
+
+template <int KS, bool SPLIT>
+__global__ __launch_bounds__(kToepColThreads, toep_col_waves(KS)) void k_toep_cols(ToepColArgs p) {
+  extern __shared__ __align__(16) unsigned char toep_smem[];
+  toep_cols_body<KS, SPLIT>(p, blockIdx.x, toep_smem, threadIdx.x);
+}
+
+template <int KS>
+__global__ __launch_bounds__(256) void k_toep_sum(ToepColArgs p) {
+  toep_sum_body<KS>(p, blockIdx.x, threadIdx.x);
+}
+
+template <int KS>
+hipError_t toep_rows1(const ToepRowArgs& a, unsigned grid, hipStream_t st) {
+  hipLaunchKernelGGL((k_toep_rows<KS>), dim3(grid), dim3(kToepRowThreads), (toep_lds_rows<KS>()), st, a);
+  return hipGetLastError();
+}
+template <int KS>
+hipError_t toep_cols1(const ToepColArgs& a, hipStream_t st) {
+  const unsigned pairs = (unsigned)((a.lgroups + 1) / 2);
+  if (a.n_parts == 1) {
+    hipLaunchKernelGGL((k_toep_cols<KS, false>), dim3(pairs), dim3(kToepColThreads),
+                       (toep_lds_cols<KS>(false)), st, a);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL((k_toep_cols<KS, true>), dim3(pairs * a.n_parts), dim3(kToepColThreads),
+                     (toep_lds_cols<KS>(true)), st, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_toep_sum<KS>), dim3((unsigned)(a.lgroups * 4 * KS)), dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+hipError_t toep_rows(int KS, const ToepRowArgs& a, unsigned grid, hipStream_t st) {
+  switch (KS) {
+    case 1: return toep_rows1<1>(a, grid, st);
+    case 2: return toep_rows1<2>(a, grid, st);
+    case 3: return toep_rows1<3>(a, grid, st);
+    case 4: return toep_rows1<4>(a, grid, st);
+    case 5: return toep_rows1<5>(a, grid, st);
+    case 6: return toep_rows1<6>(a, grid, st);
+    case 7: return toep_rows1<7>(a, grid, st);
+    case 8: return toep_rows1<8>(a, grid, st);
+  }
+  return hipErrorInvalidValue;
+}
+hipError_t toep_cols(int KS, const ToepColArgs& a, hipStream_t st) {
+  switch (KS) {
+    case 1: return toep_cols1<1>(a, st);
+    case 2: return toep_cols1<2>(a, st);
+    case 3: return toep_cols1<3>(a, st);
+    case 4: return toep_cols1<4>(a, st);
+    case 5: return toep_cols1<5>(a, st);
+    case 6: return toep_cols1<6>(a, st);
+    case 7: return toep_cols1<7>(a, st);
+    case 8: return toep_cols1<8>(a, st);
+  }
+  return hipErrorInvalidValue;
+}
+template <int KS>
+void toep_limit1() {
+  const void* fns[] = {(const void*)k_toep_rows<KS>, (const void*)k_toep_cols<KS, false>,
+                       (const void*)k_toep_cols<KS, true>};
+  for (const void* fn : fns)
+    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+      (void)hipGetLastError();
+}
+void toep_limits() {
+  toep_limit1<1>();
+  toep_limit1<2>();
+  toep_limit1<3>();
+  toep_limit1<4>();
+  toep_limit1<5>();
+  toep_limit1<6>();
+  toep_limit1<7>();
+  toep_limit1<8>();
+}
+
+__global__ __launch_bounds__(kToepBlock) void k_toep_field(ToepFieldArgs p) {
+  toep_field_body(p, blockIdx.x, threadIdx.x);
+}
+
+// The flat axis of a double-roof arm without a field stop is the identity (up
+// to unit phases): arm y's row output is the modulated field itself, arm x's
+// column output the row output.  Both in the layouts of the Toeplitz passes.
+struct ToepIdentArgs {
+  const float* field;
+  const float2* rx;        // [n_lam][n_a][D]
+  float* rbuf;             // [frames][n_lam][cblocks][n_a] blocks
+  const int2* kord;
+  float* out;
+  long long out_stride;
+  int nf, D, Dh, Dq, Nc, cblocks, N, n_a, n_lam, n_mod, o, win_lo, win_hi;
+  float w2[PWFS_MAX_LAMBDA];
+};
+
+// arm y: R[f][lam][a][x][y] = 2^20 E[f][lam][y][x] rx[lam][a][x], one thread per
+// sample (padding included), in the order of the output within a parity of y
+__global__ __launch_bounds__(kToepBlock) void k_toep_rows_ident(ToepIdentArgs p) {
+  const long long i = (long long)blockIdx.x * kToepBlock + threadIdx.x;
+  if (i >= (long long)p.nf * p.n_lam * p.n_a * p.D * 2 * p.Dq) return;
+  const int yl = (int)(i % (2 * p.Dq));
+  long long r = i / (2 * p.Dq);
+  const int x = (int)(r % p.D);
+  r /= p.D;
+  const int a = (int)(r % p.n_a);
+  r /= p.n_a;
+  const int lam = (int)(r % p.n_lam);
+  const long long f = r / p.n_lam;
+  const int yp = yl >= p.Dq ? 1 : 0, yq = yl - yp * p.Dq;
+  const size_t bf = toep_block_floats(p.Dq);
+  const float* e = p.field + (f * p.n_lam + lam) * (p.Dq / 8) * bf + toep_at(p.Dq, yl, x >> 1, x & 1);
+  const float2 w = p.rx[((long long)lam * p.n_a + a) * p.D + x];
+  const float2 v = cmul(make_float2(e[0], e[4]), w);
+  constexpr float up = (float)(1 << (kToepZExp + kToepKExp));
+  const int l = (x & 1) * p.Dq + (x >> 1);
+  float* d = p.rbuf + (((f * p.n_lam + lam) * p.cblocks + (l >> 4)) * p.n_a + a) * bf + toep_at(p.Dq, l & 15, yq, yp);
+  d[0] = up * v.x;
+  d[4] = up * v.y;
+}
+
+// arm x: I[f][o + y][X(xc)] = sum_lam w2[lam] sum_points |R[f][lam][key][xc][y]|^2
+__global__ __launch_bounds__(kToepBlock) void k_toep_cols_ident(ToepIdentArgs p) {
+  const long long i = (long long)blockIdx.x * kToepBlock + threadIdx.x;
+  if (i >= (long long)p.nf * p.Nc * p.D) return;
+  const int yl = (int)(i % p.D);
+  long long r = i / p.D;
+  const int xc = (int)(r % p.Nc);
+  const long long f = r / p.Nc;
+  const int yp = yl >= p.Dh ? 1 : 0, yq = yl - yp * p.Dh;
+  const size_t bf = toep_block_floats(p.Dq);
+  const int xw = xc >= p.D ? 1 : 0, x = xc - xw * p.D;
+  const int l = (2 * xw + (x & 1)) * p.Dq + (x >> 1);
+  const size_t at = toep_at(p.Dq, l & 15, yq, yp);
+  float acc = 0.f;
+  for (int lam = 0; lam < p.n_lam; ++lam) {
+    const float* base = p.rbuf + ((f * p.n_lam + lam) * p.cblocks + (l >> 4)) * p.n_a * bf + at;
+    float part = 0.f, val = 0.f;
+    int prev = -1;
+    for (int k = 0; k < p.n_mod; ++k) {
+      const int a = p.kord[k].y;
+      if (a != prev) {
+        const float* s = base + a * bf;
+        val = cabs2(make_float2(s[0], s[4]));
+        prev = a;
+      }
+      part += val;
+    }
+    acc += p.w2[lam] * part;
+  }
+  const int X = window_coord(xc, p.D, p.win_lo, p.win_hi);
+  p.out[f * p.out_stride + (long long)(p.o + 2 * yq + yp) * p.N + X] = acc;
+}
+
+}  // namespace
+
+// ---------------------------------------------------------- eligibility ----
+// Window-mode sensors without a field stop (a stop's kernel is neither real
+// nor sparse) and D <= 256 (the register tiles compiled), in FP32 and the split
+// precisions.  All of these take float16 hi and lo parts: bfloat16 ones, at the
+// same rate, err by 2.6e-6 where the dense DFT products err by 1.3e-6.  The
+// one-term precisions keep their own products, whose rounding is their result.
+bool toep_eligible(const pwfs_sensor_desc& d) {
+  if (d.precision == PWFS_FP16 || d.precision == PWFS_BF16) return false;
+  return !(d.flags & PWFS_F_FULL_PLANE) && !(d.fov_lod > 0.0) && d.n_pupil <= 32 * kToepMaxKS;
+}
+
+// column blocks per frame and key: windows x 2 parities x Dq lines
+static int toep_cblocks(const Geometry& g, const ToepGeom& t) { return g.Nc / g.D * 2 * t.Dq / kToepLines; }
+
+size_t toep_table_bytes(const pwfs_sensor_desc& d) {
+  if (!toep_eligible(d)) return 0;
+  const ToepGeom t = toep_geom(d);
+  const Geometry g = geometry(d);
+  return ta256(sizeof(uint16_t) * 2 * toep_table_len(t.KS)) +
+         ta256(sizeof(float) * 2 * toep_r_len(t.KS) * (size_t)g.n_lam * g.n_a) +
+         ta256(sizeof(float) * 2 * toep_r_len(t.KS) * (size_t)g.n_lam * g.n_mod);
+}
+
+// per frame: the row output, then the field (the field block of a pass sits
+// after all frames' row output)
+size_t toep_scratch_frame_bytes(const pwfs_sensor_desc& d) {
+  const ToepGeom t = toep_geom(d);
+  const Geometry g = geometry(d);
+  return sizeof(float) * toep_block_floats(t.Dq) * (size_t)g.n_lam * ((size_t)g.n_a * toep_cblocks(g, t) + t.Dq / 8);
+}
+
+// Unit sums of the split column pass, kept behind a pass's frames.  At most 256
+// MiB: beyond that many blocks the chip is full without splitting.
+static size_t toep_part_frame_bytes(const ToepGeom& t, const Geometry& g) {
+  return sizeof(float) * 2 * 8 * t.KS * 64 * (size_t)toep_cblocks(g, t) * toep_groups(g.n_mod, g.n_lam) * g.n_lam;
+}
+// Workgroups that share the units of a pair of column blocks in a pass of nf
+// frames: as many as make the launch shortest, 1 = the whole form.  One frame of
+// the 160 px sensor is 10 workgroups of 48 points otherwise (133 us; 13 us as 160
+// workgroups, and 6 us for their sum), while 100 frames of the 64 px one are 400
+// (split in two they took 63 us a pass against 53).  Model, from measured passes
+// of 1 to 32 frames: a point takes 0.55 + 0.075 KS^2 us with one wavefront on a
+// SIMD and 0.12 KS^2 us each where they share it; the split form adds a launch
+// (4 us) and a write and a read of the sums at 4 TB/s.
+static int toep_parts(const ToepGeom& t, const Geometry& g, int nf, int* per_wg) {
+  const long long pairs = ((long long)nf * toep_cblocks(g, t) + 1) / 2;
+  const int groups = toep_groups(g.n_mod, g.n_lam), units = g.n_lam * groups, waves = toep_col_waves(t.KS);
+  const size_t bytes = toep_part_frame_bytes(t, g) * (size_t)nf;
+  int parts = 1;
+  *per_wg = units;
+  if (bytes > ((size_t)256 << 20)) return 1;
+  const double k2 = (double)t.KS * t.KS, unit_points = (double)g.n_mod / groups;
+  auto cost = [&](long long wgs, int per) {
+    const long long rounds = (wgs + 256 * waves - 1) / (256 * waves);
+    const double share = (double)(rounds == 1 ? (wgs + 255) / 256 : waves);
+    return unit_points * per * (double)rounds * std::max(0.55 + 0.075 * k2, 0.12 * k2 * share);
+  };
+  double best = cost(pairs, units);
+  for (int s = 2; s <= units; ++s) {
+    const int per = (units + s - 1) / s, n = (units + per - 1) / per;
+    const double c = cost(pairs * n, per) + 4.0 + 2.0 * (double)bytes / 4e6;
+    if (c < best) {
+      best = c;
+      parts = n;
+      *per_wg = per;
+    }
+  }
+  return parts;
+}
+
+// scratch of a pass of at most chunk frames: the frames', and behind them the
+// unit sums of a pass that is split (each arm of a double roof is a pass)
+size_t toep_scratch_bytes(const pwfs_sensor_desc& d, int chunk) {
+  const ToepGeom t = toep_geom(d);
+  const size_t scratch = toep_scratch_frame_bytes(d);
+  size_t most = scratch * (size_t)chunk;
+  for (int a = 0; a < sensor_arms(d); ++a) {
+    const Geometry g = sensor_arms(d) == 2 ? arm_geometry(d, a) : geometry(d);
+    const size_t frame = toep_part_frame_bytes(t, g);
+    for (int nf = 1, per; nf <= chunk && frame * nf <= ((size_t)256 << 20); ++nf)
+      if (toep_parts(t, g, nf, &per) > 1) most = std::max(most, ta256(scratch * nf) + frame * (size_t)nf);
+  }
+  return most;
+}
+
+int toep_frames_per_pass(const pwfs_sensor_desc& d) {
+  const ToepGeom t = toep_geom(d);
+  const Geometry g = geometry(d);
+  // four rounds of resident column workgroups on 256 CUs, just not a fifth
+  const int resident = 256 * toep_col_waves(t.KS);   // of 2 blocks each
+  return std::max(1, 4 * 2 * resident / toep_cblocks(g, t));
+}
+
+int upload_toep_tables(const pwfs_sensor_desc& d, char* dst, hipStream_t st, std::vector<std::vector<char>>& keep) {
+  const ToepGeom t = toep_geom(d);
+  const Geometry g = geometry(d);
+  const int LC = toep_copy_len(t.KS), tl = toep_table_len(t.KS), rl = toep_r_len(t.KS);
+  auto c = [&](int n) { return 1.0 / (g.N * std::sin(kPiT * n / g.N)); };
+  std::vector<char> tab(ta256(sizeof(uint16_t) * 2 * tl), 0);
+  uint16_t* A = (uint16_t*)tab.data();
+  for (int p = 0; p < 2; ++p)
+    for (int w = 0; w < 2; ++w)
+      for (int u = 0; u < 32 * t.KS; ++u) {
+        // entry u holds the kernel at i' - j' = 16 KS - 1 - u, i - j = 2 (i' - j') + (2 p - 1)
+        const int del = 16 * t.KS - 1 - u;
+        double v = 0.0;
+        if (std::abs(del) < t.Dh) {
+          const int n = 2 * del + 2 * p - 1;
+          v = (w == 0 ? c(n) - c(n - g.S) : c(n + g.S) - c(n)) * (p ? -1.0 : 1.0) * (double)(1 << kToepKExp);
+        }
+        const _Float16 hi = (_Float16)v, lo = (_Float16)(v - (double)hi);
+        for (int pl = 0; pl < 2; ++pl)
+          for (int a = 0; a < 4; ++a)
+            if (u - a >= 0) std::memcpy(&A[p * tl + ((w * 2 + pl) * 4 + a) * LC + u - a], pl ? &lo : &hi, 2);
+      }
+  std::vector<TiltPoint> pts;
+  std::vector<double> key_tx;
+  tilt_points(d, pts, key_tx);
+  double wmax = 0.0;
+  for (int l = 0; l < g.n_lam; ++l) wmax = std::max(wmax, d.lambda_weight[l]);
+  // factors of one point: register 2 s + j2 = i, lane half h, lane n of 16:
+  // sample 8 i + 4 h + (n >> 1 & 3) of parity 1 - p (n < 8) or p, part n & 1
+  std::vector<std::complex<double>> z(g.D);
+  auto fill = [&](std::vector<char>& out, size_t at, double tilt, double sc, double sb, double scc) {
+    for (int x = g.D / 2; x < g.D; ++x) {
+      z[x] = std::polar(1.0, 2.0 * kPiT * sc * tilt * (x - (g.D - 1) / 2.0) / g.D);
+      z[g.D - 1 - x] = std::conj(z[x]);
+    }
+    for (int x = 1; x < g.D; x += 2) z[x] = {-z[x].imag(), z[x].real()};   // odd samples enter times i
+    float* R = (float*)out.data() + at;
+    for (int p = 0; p < 2; ++p)
+      for (int jq = 0; jq < t.Dh; ++jq) {
+        float* r = R + (size_t)p * rl + (((jq >> 5) * 2 + (jq >> 2 & 1)) * 16 + 2 * (jq & 3)) * 4 + (jq >> 3 & 3);
+        const std::complex<double> o = z[2 * jq + 1 - p] * sb, w = z[2 * jq + p] * scc;
+        r[0] = (float)o.real();
+        r[4] = (float)o.imag();
+        r[32] = (float)w.real();
+        r[36] = (float)w.imag();
+      }
+  };
+  std::vector<char> rx(ta256(sizeof(float) * 2 * rl * (size_t)g.n_lam * g.n_a), 0);
+  std::vector<char> ry(ta256(sizeof(float) * 2 * rl * (size_t)g.n_lam * g.n_mod), 0);
+  const double up = std::ldexp(1.0, kToepZExp + kToepKExp);
+  for (int l = 0; l < g.n_lam; ++l) {
+    const double sc = d.lambda_ref_nm / d.lambda_nm[l];
+    const double amp = std::sqrt(d.lambda_weight[l] / wmax);
+    for (int a = 0; a < g.n_a; ++a)
+      fill(rx, ((size_t)l * g.n_a + a) * 2 * rl, key_tx[a], sc, std::ldexp(1.0, kToepZExp), 0.5 * up);
+    for (int k = 0; k < g.n_mod; ++k)
+      fill(ry, ((size_t)l * g.n_mod + k) * 2 * rl, pts[k].ty, sc, amp * std::ldexp(1.0, -kToepKExp), 0.5 * amp);
+  }
+  for (std::vector<char>* v : {&tab, &rx, &ry}) {
+    const size_t bytes = v->size();
+    keep.push_back(std::move(*v));
+    const hipError_t e = hipMemcpyAsync(dst, keep.back().data(), bytes, hipMemcpyHostToDevice, st);
+    if (e != hipSuccess) {
+      set_last_error("hipMemcpyAsync(Toeplitz tables)");
+      return PWFS_EHIP;
+    }
+    dst += bytes;
+  }
+  return PWFS_OK;
+}
+
+void toep_prepare() {
+  toep_limits();
+  toep_hetero_limit();
+}
+
+namespace {
+
+// Arguments of the three passes of one sensor over nf frames.
+struct ToepPass {
+  ToepFieldArgs fa;
+  ToepRowArgs ra;
+  ToepColArgs ca;
+  unsigned grid_field, grid_rows, grid_cols;
+};
+
+ToepPass toep_pass(const SensorPlan& sp, const ToepGeom& t, const float* opd, long long opd_stride, float* out,
+                   long long out_stride, int nf, float2* rbuf, int row_target) {
+  const Geometry& g = sp.g;
+  ToepPass tp{};
+  float* R = (float*)rbuf;
+  const int cblocks = toep_cblocks(g, t);
+  float* field = R + (size_t)nf * g.n_lam * g.n_a * cblocks * toep_block_floats(t.Dq);
+  const char* tb = (const char*)sp.dev[R_TOEP];
+  const uint16_t* atab = (const uint16_t*)tb;
+  tb += ta256(sizeof(uint16_t) * 2 * toep_table_len(t.KS));
+  const float* rx = (const float*)tb;
+  tb += ta256(sizeof(float) * 2 * toep_r_len(t.KS) * (size_t)g.n_lam * g.n_a);
+  const float* ry = (const float*)tb;
+
+  ToepFieldArgs& fa = tp.fa;
+  fa.opd = opd;
+  fa.amp = (const float*)sp.dev[R_AMP];
+  fa.field = field;
+  fa.opd_stride = opd_stride;
+  fa.D = g.D;
+  fa.Dh = t.Dh;
+  fa.Dq = t.Dq;
+  fa.n_lam = g.n_lam;
+  for (int l = 0; l < g.n_lam; ++l) fa.two_pi_over_lam[l] = 2.0 * kPiT / sp.desc.lambda_nm[l];
+  tp.grid_field = (unsigned)(nf * g.n_lam * ((t.Dq * t.Dq + kToepBlock - 1) / kToepBlock));
+
+  ToepRowArgs& ra = tp.ra;
+  ra.field = field;
+  ra.rbuf = R;
+  ra.atab = atab;
+  ra.rtab = rx;
+  ra.Dh = t.Dh;
+  ra.Dq = t.Dq;
+  ra.cblocks = cblocks;
+  ra.n_a = g.n_a;
+  ra.n_lam = g.n_lam;
+  ra.lgroups = nf * (t.Dq / 8);
+  // split the keys so that a pass has row_target workgroups (two keys at a time each)
+  const long long base = (long long)ra.lgroups * g.n_lam;
+  const int groups =
+      (int)std::min<long long>((g.n_a + 1) / 2, std::max<long long>(1, (row_target + base - 1) / base));
+  ra.ag = (g.n_a + groups - 1) / groups;
+  ra.n_agroups = (g.n_a + ra.ag - 1) / ra.ag;
+  tp.grid_rows = (unsigned)(base * ra.n_agroups);
+
+  ToepColArgs& ca = tp.ca;
+  ca.rbuf = R;
+  ca.atab = atab;
+  ca.rtab = ry;
+  ca.kord = (const int2*)sp.dev[R_AK];
+  ca.out = out;
+  ca.out_stride = out_stride;
+  ca.Dh = t.Dh;
+  ca.Dq = t.Dq;
+  ca.cblocks = cblocks;
+  ca.n_a = g.n_a;
+  ca.n_lam = g.n_lam;
+  ca.n_mod = g.n_mod;
+  ca.N = g.N;
+  ca.win_lo = g.win_lo;
+  ca.win_hi = g.win_hi;
+  ca.wy_lo = g.wy_lo;
+  ca.wy_hi = g.wy_hi;
+  ca.lgroups = nf * cblocks;
+  ca.groups = toep_groups(g.n_mod, g.n_lam);
+  ca.units = g.n_lam * ca.groups;
+  ca.n_parts = 1;
+  double wmax = 0.0;
+  for (int l = 0; l < g.n_lam; ++l) wmax = std::max(wmax, sp.desc.lambda_weight[l]);
+  ca.scale = (float)((sp.arms == 2 ? 0.5 : 1.0) * wmax / ((double)g.n_mod * sp.sumA2) *
+                     std::ldexp(1.0, -2 * (kToepZExp + kToepKExp)));
+  tp.grid_cols = (unsigned)((ca.lgroups + 1) / 2);
+  return tp;
+}
+
+int toep_failed(hipError_t e, const char* what) {
+  char msg[160];
+  snprintf(msg, sizeof msg, "launch %s: %s", what, hipGetErrorString(e));
+  set_last_error(msg);
+  return PWFS_EHIP;
+}
+
+size_t toep_lds_of(int KS) {
+  switch (KS) {
+    case 1: return std::max(toep_lds_rows<1>(), toep_lds_cols<1>(false));
+    case 2: return std::max(toep_lds_rows<2>(), toep_lds_cols<2>(false));
+    case 3: return std::max(toep_lds_rows<3>(), toep_lds_cols<3>(false));
+    case 4: return std::max(toep_lds_rows<4>(), toep_lds_cols<4>(false));
+    case 5: return std::max(toep_lds_rows<5>(), toep_lds_cols<5>(false));
+    case 6: return std::max(toep_lds_rows<6>(), toep_lds_cols<6>(false));
+    case 7: return std::max(toep_lds_rows<7>(), toep_lds_cols<7>(false));
+    default: return std::max(toep_lds_rows<8>(), toep_lds_cols<8>(false));
+  }
+}
+
+}  // namespace
+
+int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, float* out, long long out_stride,
+                 int nf, float2* rbuf, hipStream_t st, Prof* prof) {
+  const Geometry& g = sp.g;
+  const ToepGeom t = toep_geom(sp.desc);
+  ToepPass tp = toep_pass(sp, t, opd, opd_stride, out, out_stride, nf, rbuf, 512);
+  hipError_t e;
+  int slot = prof->begin(st);
+  hipLaunchKernelGGL(k_toep_field, dim3(tp.grid_field), dim3(kToepBlock), 0, st, tp.fa);
+  if ((e = hipGetLastError()) != hipSuccess) return toep_failed(e, "k_toep_field");
+  prof->end(slot, st, K_FIELD);
+
+  ToepIdentArgs ia{};
+  if (sp.ident) {
+    ia.field = tp.ra.field;
+    ia.rx = (const float2*)sp.dev[R_RX];
+    ia.rbuf = tp.ra.rbuf;
+    ia.kord = tp.ca.kord;
+    ia.out = out;
+    ia.out_stride = out_stride;
+    ia.nf = nf;
+    ia.D = g.D;
+    ia.Dh = t.Dh;
+    ia.Dq = t.Dq;
+    ia.Nc = g.Nc;
+    ia.cblocks = tp.ca.cblocks;
+    ia.N = g.N;
+    ia.n_a = g.n_a;
+    ia.n_lam = g.n_lam;
+    ia.n_mod = g.n_mod;
+    ia.o = g.o;
+    ia.win_lo = g.win_lo;
+    ia.win_hi = g.win_hi;
+    for (int l = 0; l < g.n_lam; ++l)
+      ia.w2[l] = (float)(0.5 * sp.desc.lambda_weight[l] / ((double)g.n_mod * sp.sumA2) *
+                         std::ldexp(1.0, -2 * (kToepZExp + kToepKExp)));
+  }
+
+  slot = prof->begin(st);
+  if (sp.ident == 2) {
+    const long long n = (long long)nf * g.n_lam * g.n_a * g.D * 2 * t.Dq;
+    hipLaunchKernelGGL(k_toep_rows_ident, dim3((unsigned)((n + kToepBlock - 1) / kToepBlock)), dim3(kToepBlock), 0,
+                       st, ia);
+    e = hipGetLastError();
+  } else {
+    e = toep_rows(t.KS, tp.ra, tp.grid_rows, st);
+  }
+  if (e != hipSuccess) return toep_failed(e, "k_toep_rows");
+  prof->end(slot, st, K_ROWS);
+
+  slot = prof->begin(st);
+  if (sp.ident == 1) {
+    const long long n = (long long)nf * g.Nc * g.D;
+    hipLaunchKernelGGL(k_toep_cols_ident, dim3((unsigned)((n + kToepBlock - 1) / kToepBlock)), dim3(kToepBlock), 0,
+                       st, ia);
+    e = hipGetLastError();
+  } else {
+    tp.ca.n_parts = toep_parts(t, g, nf, &tp.ca.per_wg);
+    tp.ca.part = (float*)((char*)rbuf + ta256(toep_scratch_frame_bytes(sp.desc) * (size_t)nf));
+    e = toep_cols(t.KS, tp.ca, st);
+  }
+  if (e != hipSuccess) return toep_failed(e, "k_toep_cols");
+  prof->end(slot, st, sp.desc.precision == PWFS_FP32 ? K_COLS : K_MFMA);
+  return PWFS_OK;
+}
+
+// One persistent launch over the Toeplitz sensors of a plan (`which`, indices
+// into the plan) for frames [f0, f0 + nf).  `counters` are cleared by the caller.
+int forward_toep_hetero(pwfs_plan_s* p, const std::vector<int>& which, const float* opd, int f0, int nf, float* out,
+                        int* counters, int* flag, hipStream_t st) {
+  ToepHeteroArgs ha{};
+  size_t lds = 0;
+  std::vector<std::pair<double, int>> cost;
+  for (size_t i = 0; i < which.size(); ++i) {
+    const SensorPlan& sp = p->s[which[i]];
+    const ToepGeom t = toep_geom(sp.desc);
+    const ToepPass tp = toep_pass(sp, t, opd + sp.opd_offset + (long long)f0 * p->opd_stride,
+                                  (long long)p->opd_stride, out + sp.int_offset + (long long)f0 * p->int_stride,
+                                  (long long)p->int_stride, nf, sp.rbuf, p->tune.row_groups);
+    ha.field[i] = tp.fa;
+    ha.rows[i] = tp.ra;
+    ha.cols[i] = tp.ca;
+    ha.ks[i] = t.KS;
+    ha.n_items[0][i] = (int)tp.grid_field;
+    ha.n_items[1][i] = (int)tp.grid_rows;
+    ha.n_items[2][i] = (int)tp.grid_cols;
+    lds = std::max(lds, toep_lds_of(t.KS));
+    cost.push_back({-(double)sp.g.n_mod * sp.g.n_lam * sp.g.D * sp.g.D, (int)i});
+    for (int k = 0; k < 3; ++k) ha.total += ha.n_items[k][i];
+  }
+  std::sort(cost.begin(), cost.end());
+  for (size_t i = 0; i < cost.size(); ++i) ha.order[i] = cost[i].second;   // largest sensors claim first
+  ha.n_sensors = (int)which.size();
+  ha.counters = counters;
+  ha.flag = flag;
+  ha.spin_limit = p->tune.spin_limit != 0 ? p->tune.spin_limit : (1 << 24);
+  const int slot = p->prof.begin(st);
+  const hipError_t e = toep_hetero_launch(ha, p->n_cu * std::max(1, p->tune.wg_per_cu), lds, st);
+  if (e != hipSuccess) return toep_failed(e, "k_toep_hetero");
+  p->prof.end(slot, st, K_HETERO);
+  return PWFS_OK;
+}
+
+}  // namespace pwfs
