@@ -279,20 +279,35 @@ __global__ __launch_bounds__(256) void k_split(SplitArgs p) {
   put16(p.dst, p.plane, off, v, p.planes);
 }
 
-// column sums of an fp32 [rows][ld] matrix over its first `rows` rows
+// Column sums of an fp32 [rows][ld] matrix over its first `rows` rows (ld a
+// multiple of 4).  A workgroup takes 16 columns: 4 lanes of 4 columns each, 64
+// lanes down the rows, whose sums are added in LDS.  One thread per column was a
+// serial chain of loads on 4 to 13 workgroups (236 us for 1024 rows, now 5 us).
+constexpr int kColsumCols = 16;
 __global__ __launch_bounds__(256) void k_colsum(const float* x, long long ld, int rows, int cols, float* out) {
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= cols) return;
-  float s = 0.f;
-  for (int r = 0; r < rows; ++r) s += x[(long long)r * ld + c];
-  out[c] = s;
+  __shared__ f32x4_t s_sum[64][4];
+  const int q = threadIdx.x & 3, r0 = threadIdx.x >> 2;
+  const int c = blockIdx.x * kColsumCols + 4 * q;
+  f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+  if (c < cols)
+#pragma unroll 4
+    for (int r = r0; r < rows; r += 64) s += *(const f32x4_t*)(x + (long long)r * ld + c);
+  s_sum[r0][q] = s;
+  __syncthreads();
+  for (int w = 32; w > 0; w >>= 1) {
+    if (r0 < w) s_sum[r0][q] += s_sum[r0 + w][q];
+    __syncthreads();
+  }
+  if (r0 == 0)
+    for (int e = 0; e < 4 && c + e < cols; ++e) out[c + e] = s_sum[0][q][e];
 }
 
-__global__ void k_loss_reduce(const double* part, int n, float scale, float* loss) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// one wavefront
+__global__ __launch_bounds__(64) void k_loss_reduce(const double* part, int n, float scale, float* loss) {
   double s = 0.0;
-  for (int i = 0; i < n; ++i) s += part[i];
-  *loss = (float)(s * scale);
+  for (int i = threadIdx.x; i < n; i += 64) s += part[i];
+  for (int w = 32; w > 0; w >>= 1) s += __shfl_down(s, w, 64);
+  if (threadIdx.x == 0) *loss = (float)(s * scale);
 }
 
 struct AdamArgs {
@@ -934,8 +949,8 @@ extern "C" int pwfs_mlp_grad(pwfs_mlp_t m, const float* x, const float* t, int b
     g.c = m->gW[l];
     g.ldc = m->P[l];
     if ((rc = gemm_dispatch<E_STORE>(pl, g, st))) return rc;
-    hipLaunchKernelGGL(k_colsum, dim3((unsigned)((m->n[l + 1] + 255) / 256)), dim3(256), 0, st, m->dZ[l + 1],
-                       (long long)m->P[l + 1], batch, m->n[l + 1], m->gb[l]);
+    hipLaunchKernelGGL(k_colsum, dim3((unsigned)((m->n[l + 1] + kColsumCols - 1) / kColsumCols)), dim3(256), 0, st,
+                       m->dZ[l + 1], (long long)m->P[l + 1], batch, m->n[l + 1], m->gb[l]);
     if (hipGetLastError() != hipSuccess) return mfail(PWFS_EHIP, "launch k_colsum");
     if (l == 0) break;
     // G_l = (G_{l+1} W_l) * gelu'(Z_l) : A = G_{l+1} [batch][P_{l+1}], B = Wqt_l [P_l][P_{l+1}]
