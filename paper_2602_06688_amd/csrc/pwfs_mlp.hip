@@ -92,38 +92,74 @@ __device__ __forceinline__ void put16(uint16_t* base, long long plane, long long
   }
 }
 
-// the epilogue of one output element (m, n) of a product whose accumulated
-// value is v; lsum collects the squared error (E_OUTPUT with a target)
-template <int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, int m, int n, float v, double& lsum) {
-  if constexpr (EPI == E_STORE) {
-    float* cp = p.c + (long long)m * p.ldc + n;
-    *cp = (p.beta != 0.f) ? p.alpha * v + p.beta * *cp : p.alpha * v;
-  } else if constexpr (EPI == E_HIDDEN) {
-    const float zz = v + p.bias[n];
-    const float hv = gelu_f(zz);
-    put16(p.h, p.h_plane, (long long)m * p.ldh + n, hv, p.planes_out);
-    // the pre-activation and the transposed copy serve the backward
-    // pass only (absent in inference)
-    if (p.z) p.z[(long long)m * p.ldz + n] = zz;
-    if (p.ht) put16(p.ht, p.ht_plane, (long long)n * p.ldht + m, hv, p.planes_out);
-  } else if constexpr (EPI == E_OUTPUT) {
-    const float y = v + p.bias[n];
-    if (p.c) p.c[(long long)m * p.ldc + n] = p.alpha * y;
-    if (p.target) {
-      const float d = y - p.target[(long long)m * p.ldt + n] * p.tscale;
-      lsum += (double)d * d;
-      const float g = p.gscale * d;
-      p.z[(long long)m * p.ldz + n] = g;
-      put16(p.h, p.h_plane, (long long)m * p.ldh + n, g, p.planes_out);
-      put16(p.ht, p.ht_plane, (long long)n * p.ldht + m, g, p.planes_out);
-    }
-  } else {  // E_DHIDDEN
-    const float g = v * gelu_grad_f(p.zprev[(long long)m * p.ldzp + n]);
-    p.z[(long long)m * p.ldz + n] = g;
-    put16(p.h, p.h_plane, (long long)m * p.ldh + n, g, p.planes_out);
-    put16(p.ht, p.ht_plane, (long long)n * p.ldht + m, g, p.planes_out);
+// four elements down a column of a transposed 16-bit copy, one 8-byte store
+// (off a multiple of 4 elements)
+__device__ __forceinline__ void put16x4(uint16_t* base, long long plane, long long off, const float (&v)[4],
+                                        int planes) {
+  uint16_t hi[4], lo[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (planes == 2) split16<false>(v[r], hi[r], lo[r]);
+    else hi[r] = f32_to_bf16_rne(v[r]);
   }
+  *(uint2*)(base + off) = make_uint2(hi[0] | (uint32_t)hi[1] << 16, hi[2] | (uint32_t)hi[3] << 16);
+  if (planes == 2)
+    *(uint2*)(base + plane + off) = make_uint2(lo[0] | (uint32_t)lo[1] << 16, lo[2] | (uint32_t)lo[3] << 16);
+}
+
+// the epilogue of the outputs (m .. m + 3, n) of a product whose accumulated
+// values are v (m a multiple of 4; rows from p.M on are not written); lsum
+// collects the squared error (E_OUTPUT with a target).  Transposed copies exist
+// in training only, whose M (the batch) and ldht are multiples of 32: they leave
+// in 8-byte stores.
+template <int EPI>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, int m, int n, const float (&v)[4], double& lsum) {
+  float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    if (m + r >= p.M) break;
+    const long long mr = m + r;
+    if constexpr (EPI == E_STORE) {
+      float* cp = p.c + mr * p.ldc + n;
+      *cp = (p.beta != 0.f) ? p.alpha * v[r] + p.beta * *cp : p.alpha * v[r];
+    } else if constexpr (EPI == E_HIDDEN) {
+      const float zz = v[r] + p.bias[n];
+      t[r] = gelu_f(zz);
+      put16(p.h, p.h_plane, mr * p.ldh + n, t[r], p.planes_out);
+      // the pre-activation and the transposed copy serve the backward
+      // pass only (absent in inference)
+      if (p.z) p.z[mr * p.ldz + n] = zz;
+    } else if constexpr (EPI == E_OUTPUT) {
+      const float y = v[r] + p.bias[n];
+      if (p.c) p.c[mr * p.ldc + n] = p.alpha * y;
+      if (p.target) {
+        const float d = y - p.target[mr * p.ldt + n] * p.tscale;
+        lsum += (double)d * d;
+        t[r] = p.gscale * d;
+        p.z[mr * p.ldz + n] = t[r];
+        put16(p.h, p.h_plane, mr * p.ldh + n, t[r], p.planes_out);
+      }
+    } else {  // E_DHIDDEN
+      t[r] = v[r] * gelu_grad_f(p.zprev[mr * p.ldzp + n]);
+      p.z[mr * p.ldz + n] = t[r];
+      put16(p.h, p.h_plane, mr * p.ldh + n, t[r], p.planes_out);
+    }
+  }
+  if constexpr (EPI != E_STORE)
+    if (p.ht && m < p.M) put16x4(p.ht, p.ht_plane, (long long)n * p.ldht + m, t, p.planes_out);
+}
+
+// the squared error of a workgroup of 256 lanes
+__device__ __forceinline__ void loss_partial(const GemmArgs& p, double lsum, int tid) {
+  if (!p.loss_part) return;
+  __shared__ double red[256];
+  red[tid] = lsum;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (tid < w) red[tid] += red[tid + w];
+    __syncthreads();
+  }
+  if (tid == 0) p.loss_part[blockIdx.x] = red[0];
 }
 
 template <int NPL, int EPI, int BK>
@@ -159,25 +195,102 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs p) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
+      for (int e = 0; e < 16; e += 4) {
         int row, col;
         E::coord(tid, i, j, e, row, col);
         const int m = m0 + row, n = n0 + col;
         if (m >= p.M || n >= p.N) continue;
-        gemm_epilogue<EPI>(p, m, n, eng.value(i, j, e), lsum);
+        const float v[4] = {eng.value(i, j, e), eng.value(i, j, e + 1), eng.value(i, j, e + 2), eng.value(i, j, e + 3)};
+        gemm_epilogue<EPI>(p, m, n, v, lsum);
       }
-  if constexpr (EPI == E_OUTPUT) {
-    if (p.loss_part) {
-      __shared__ double red[256];
-      red[tid] = lsum;
+  if constexpr (EPI == E_OUTPUT) loss_partial(p, lsum, tid);
+}
+
+// Products with few tiles (training batches, short inference batches): 64 x 64
+// tiles, one 32 x 32 quarter per wavefront, so that they reach all CUs; their K
+// steps are then too short to hide a load, and three of them are kept in flight
+// in registers.  Each element sees the matrix products of k_gemm in the same
+// order, so both give the same bits.
+constexpr int kSmallTile = 64;
+template <int NPL, int BK>
+constexpr int gemm_small_stage() { return NPL * 2 * kSmallTile * (BK + 8); }   // 16-bit elements, A planes, then B
+
+template <int NPL, int EPI, int BK>
+__global__ __launch_bounds__(256) void k_gemm_small(GemmArgs p) {
+  using E = MfmaTile<NPL, false, BK>;
+  constexpr int DEPTH = 3, CPR = BK / 8, RPP = 256 / CPR, CH = NPL * 2 * kSmallTile / RPP, LROW = BK + 8;
+  __shared__ __align__(16) uint16_t lds[2][gemm_small_stage<NPL, BK>()];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
+  const int nt = blockIdx.x % p.ntiles, mt = blockIdx.x / p.ntiles;
+  const int m0 = mt * kSmallTile, n0 = nt * kSmallTile;
+  const int nk1 = p.K / BK, steps = nk1 + p.K2 / BK;
+  const int kq = (tid % CPR) * 8;
+  // chunk h of a step: stage row tid / CPR + RPP h (A planes, then B planes)
+  auto chunk = [&](int h, int s) {
+    const int row = tid / CPR + RPP * h, pl = row / kSmallTile % NPL, r = row % kSmallTile;
+    const bool is_a = RPP * h < NPL * kSmallTile, seg2 = s >= nk1;
+    const long long k = (long long)(seg2 ? s - nk1 : s) * BK + kq;
+    if (is_a) {
+      const long long ra = min(m0 + r, p.M - 1);
+      return *(const u32x4_t*)(seg2 ? p.a2 + pl * p.a2_plane + ra * p.lda2 + k : p.a + pl * p.a_plane + ra * p.lda + k);
+    }
+    const long long rb = min(n0 + r, p.N - 1);
+    return *(const u32x4_t*)(seg2 ? p.b2 + pl * p.b2_plane + rb * p.ldb2 + k : p.b + pl * p.b_plane + rb * p.ldb + k);
+  };
+  u32x4_t buf[DEPTH][CH];
+  auto fetch = [&](u32x4_t (&b)[CH], int s) {   // steps past the end load the last one, unused
+#pragma unroll
+    for (int h = 0; h < CH; ++h) b[h] = chunk(h, min(s, steps - 1));
+  };
+  auto stash = [&](const u32x4_t (&b)[CH], uint16_t* stage) {
+#pragma unroll
+    for (int h = 0; h < CH; ++h) *(u32x4_t*)(stage + (tid / CPR + RPP * h) * LROW + kq) = b[h];
+  };
+  f32x16_t acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  auto compute = [&](const uint16_t* stage) {
+    const int r = lane & 31, kh = (lane >> 5) * 8;
+#pragma unroll
+    for (int s = 0; s < BK / 16; ++s) {
+      u32x4_t fa[NPL], fb[NPL];
+#pragma unroll
+      for (int pl = 0; pl < NPL; ++pl) {
+        fa[pl] = *(const u32x4_t*)(stage + (pl * kSmallTile + wm * 32 + r) * LROW + s * 16 + kh);
+        fb[pl] = *(const u32x4_t*)(stage + ((NPL + pl) * kSmallTile + wn * 32 + r) * LROW + s * 16 + kh);
+      }
+      acc = E::mma(fa[0], fb[0], acc);
+      if constexpr (NPL == 2) {
+        acc = E::mma(fa[0], fb[1], acc);
+        acc = E::mma(fa[1], fb[0], acc);
+      }
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < DEPTH; ++u) fetch(buf[u], u);
+  stash(buf[0], lds[0]);
+  fetch(buf[0], DEPTH);
+  __syncthreads();
+  for (int st = 0; st < steps; st += DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; ++u) {
+      if (st + u >= steps) break;
+      compute(lds[(st + u) & 1]);
+      stash(buf[(u + 1) % DEPTH], lds[(st + u + 1) & 1]);
+      fetch(buf[(u + 1) % DEPTH], st + u + 1 + DEPTH);
       __syncthreads();
-      for (int w = 128; w > 0; w >>= 1) {
-        if (tid < w) red[tid] += red[tid + w];
-        __syncthreads();
-      }
-      if (tid == 0) p.loss_part[blockIdx.x] = red[0];
     }
   }
+  double lsum = 0.0;
+  const int n = n0 + wn * 32 + (lane & 31);
+  if (n < p.N)
+#pragma unroll
+    for (int e = 0; e < 16; e += 4) {
+      const int m = m0 + wm * 32 + 8 * (e >> 2) + 4 * (lane >> 5);
+      const float v[4] = {acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
+      if (m < p.M) gemm_epilogue<EPI>(p, m, n, v, lsum);
+    }
+  if constexpr (EPI == E_OUTPUT) loss_partial(p, lsum, tid);
 }
 
 // Large one-plane products (inference passes of the network, big plain
@@ -249,12 +362,13 @@ __global__ __launch_bounds__(64 * (2 * BN / 64 + 4)) void k_gemm_ws(GemmArgs p) 
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
+      for (int e = 0; e < 16; e += 4) {
         // accumulator layout of the 32 x 32 tile (i, j) of this quarter
-        const int m = m0 + wm * 64 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+        const int m = m0 + wm * 64 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5);
         const int n = n0 + wn * 64 + j * 32 + (lane & 31);
         if (m >= p.M || n >= p.N) continue;
-        gemm_epilogue<EPI>(p, m, n, eng.value(i, j, e), lsum);
+        const float v[4] = {eng.value(i, j, e), eng.value(i, j, e + 1), eng.value(i, j, e + 2), eng.value(i, j, e + 3)};
+        gemm_epilogue<EPI>(p, m, n, v, lsum);
       }
 }
 
@@ -383,6 +497,17 @@ int gemm_launch(const GemmArgs& a0, hipStream_t st) {
   return PWFS_OK;
 }
 
+template <int NPL, int EPI, int BK>
+int gemm_small_launch(const GemmArgs& a0, hipStream_t st) {
+  GemmArgs a = a0;
+  a.mtiles = (a.M + kSmallTile - 1) / kSmallTile;
+  a.ntiles = (a.N + kSmallTile - 1) / kSmallTile;
+  hipLaunchKernelGGL((k_gemm_small<NPL, EPI, BK>), dim3((unsigned)(a.mtiles * a.ntiles)), dim3(256), 0, st, a);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return mfail(PWFS_EHIP, "launch k_gemm_small: %s", hipGetErrorString(e));
+  return PWFS_OK;
+}
+
 // One-plane products whose K is a multiple of 64 take K steps of 64 (8
 // matrix products per wavefront between barriers instead of 4, so load
 // latency hides behind them; same products in the same order, same bits).
@@ -415,8 +540,22 @@ int gemm_ws_launch(const GemmArgs& a0, hipStream_t st) {
 // and gradient epilogues) take the 256-lane tiles.
 constexpr int kWsMinTiles = 512, kWsWideTiles = 1024;
 
+// Products of fewer 128 x 128 tiles than two rounds of the chip take 64 x 64
+// tiles (training products of 64 to 200 tiles: 64 us -> 25 to 36 us).  Two-plane
+// products do three times the work per load and only gain while tiles leave CUs
+// idle (400 x 7596 x 576, 240 tiles: 38 us in 128-tiles, 44 us in 64-tiles).
+bool small_tiles(int planes, int M, int N) {
+  const long long tiles = (long long)((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTile - 1) / kGemmTile);
+  return tiles < (planes == 2 ? 192 : 512);
+}
+
 template <int EPI>
 int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
+  if (small_tiles(planes, a.M, a.N)) {
+    if (planes == 2) return gemm_small_launch<2, EPI, 32>(a, st);
+    if (a.K % 64 != 0 || a.K2 % 64 != 0) return gemm_small_launch<1, EPI, 32>(a, st);
+    return gemm_small_launch<1, EPI, 64>(a, st);
+  }
   if (planes == 2) return gemm_launch<2, EPI, 32>(a, st);
   if (a.K % 64 != 0 || a.K2 % 64 != 0) return gemm_launch<1, EPI, 32>(a, st);
   if constexpr (EPI != E_DHIDDEN) {
@@ -596,6 +735,9 @@ struct MlpLayout {
 };
 
 // sizes of every region, in order; `cb` is called with each region's bytes
+// squared-error partials: one per tile of the output layer, the small ones at most
+int loss_parts_of(int Bm, int P) { return ((Bm + kSmallTile - 1) / kSmallTile) * ((P + kSmallTile - 1) / kSmallTile); }
+
 template <class CB>
 void mlp_regions(int L, const std::vector<int>& P, int Bm, int planes, CB cb) {
   for (int l = 0; l < L; ++l) {
@@ -617,8 +759,7 @@ void mlp_regions(int L, const std::vector<int>& P, int Bm, int planes, CB cb) {
   cb(4 * (size_t)Bm * P[L]);                   // Y
   cb(4 * (size_t)P[L] * P[0]);                 // C
   cb(2 * planes * (size_t)P[L] * P[0]);        // Cq
-  const int tiles = ((Bm + 127) / 128) * ((P[L] + 127) / 128);
-  cb(8 * (size_t)tiles);                       // loss partials
+  cb(8 * (size_t)loss_parts_of(Bm, P[L]));     // loss partials
 }
 
 int mlp_check(int L, const int32_t* sizes, int Bm, int precision, std::vector<int>& n, std::vector<int>& P) {
@@ -693,7 +834,7 @@ extern "C" int pwfs_mlp_create(int L, const int32_t* sizes, int max_batch, int p
   m->C = (float*)reg[r++];
   m->Cq = (uint16_t*)reg[r++];
   m->loss_part = (double*)reg[r++];
-  m->loss_parts = ((max_batch + 127) / 128) * ((m->P[L] + 127) / 128);
+  m->loss_parts = loss_parts_of(max_batch, m->P[L]);
   // everything starts at zero: padding of every buffer must stay zero
   const hipError_t e = hipMemsetAsync(ws, 0, need, (hipStream_t)stream);
   if (e != hipSuccess) {
@@ -927,7 +1068,8 @@ extern "C" int pwfs_mlp_grad(pwfs_mlp_t m, const float* x, const float* t, int b
   const int L = m->L, pl = m->planes;
   int rc = mlp_forward(m, x, batch, m->Y, 1.f, t, tscale, st);
   if (rc) return rc;
-  const int tiles = ((batch + 127) / 128) * ((m->n[L] + 127) / 128);
+  const int tile = small_tiles(pl, batch, m->n[L]) ? kSmallTile : kGemmTile;
+  const int tiles = ((batch + tile - 1) / tile) * ((m->n[L] + tile - 1) / tile);
   if (loss) {
     hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(64), 0, st, m->loss_part, tiles,
                        1.f / ((float)batch * (float)m->n[L]), loss);

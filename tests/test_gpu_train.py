@@ -29,3 +29,20 @@ def test_output_bias_gradient_and_loss(n_out, B):
     gb = g.cpu().numpy()[-n_out:].astype(np.float64)
     assert (np.abs(gb - dy.sum(0)) <= (B + 8) * 2.0 ** -24 * np.abs(dy).sum(0)).all()
     assert abs(float(loss.item()) / (d * d).mean() - 1.0) <= 1e-6
+
+
+@pytest.mark.parametrize("prec", ["BF16", "BF16X3"])
+@pytest.mark.parametrize("M,N,K", [(1, 1024, 32), (63, 1024, 96), (65, 1000, 64), (200, 1023, 192), (4032, 1024, 416)])
+def test_small_tiles_give_the_bits_of_the_large_ones(prec, M, N, K):
+    """Rows of a product computed alone (64 x 64 tiles) and inside one of 8192
+    rows (the tiles of products that fill the chip): every element adds the same
+    matrix products in the same order."""
+    from paper_2602_06688_amd import pwfs as P
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    A = torch.randn(8192, K, device="cuda", generator=g)
+    B = torch.randn(N, K, device="cuda", generator=g)
+    print(f"[gpu] gemm {prec} {M} of 8192 x {N} x {K}", flush=True)
+    whole = P.gemm(A, B, precision=getattr(P, prec))
+    part = P.gemm(A[:M].contiguous(), B, precision=getattr(P, prec))
+    torch.cuda.synchronize()
+    assert torch.equal(part, whole[:M])
