@@ -372,25 +372,58 @@ __global__ __launch_bounds__(64 * (2 * BN / 64 + 4)) void k_gemm_ws(GemmArgs p) 
       }
 }
 
-// fp32 [rows][cols] (row stride ld) -> 16-bit planes [rows][Kp], zero padding;
-// with `transpose`, planes [cols][ldo] hold the transpose (row index = col)
+// fp32 [rows][cols] (row stride ld) -> 16-bit planes [rows][ldo], zero padding up
+// to Kp columns (a multiple of 4); with dst_t also the transpose [Kp][ldo_t]
+// (rows a multiple of 4 then).  Up to two matrices in one launch.
 struct SplitArgs {
   const float* src;
   long long ld;
   uint16_t* dst;
   long long plane, ldo;
-  int rows, cols, Kp, planes, transpose;
+  int rows, cols, Kp, planes;
   float scale;
+  uint16_t* dst_t;
+  long long plane_t, ldo_t;
+  unsigned wgs;   // workgroups
+};
+struct SplitPair {
+  SplitArgs s[2];
 };
 
-__global__ __launch_bounds__(256) void k_split(SplitArgs p) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long total = (long long)p.rows * p.Kp;
-  if (i >= total) return;
-  const int r = (int)(i / p.Kp), k = (int)(i % p.Kp);
-  const float v = (k < p.cols) ? p.src[(long long)r * p.ld + k] * p.scale : 0.f;
-  const long long off = p.transpose ? (long long)k * p.ldo + r : (long long)r * p.ldo + k;
-  put16(p.dst, p.plane, off, v, p.planes);
+// A thread takes four columns of a row (one 16-byte load where the rows allow
+// it), or, with a transpose, four rows of a column: 8-byte stores into the
+// transpose, 2-byte ones side by side into the rows.
+__global__ __launch_bounds__(256) void k_split(SplitPair a) {
+  const bool second = blockIdx.x >= a.s[0].wgs;
+  const SplitArgs& p = a.s[second ? 1 : 0];
+  const long long i = (long long)(blockIdx.x - (second ? a.s[0].wgs : 0u)) * 256 + threadIdx.x;
+  float v[4];
+  if (p.dst_t) {
+    const long long rq = i / p.Kp;
+    const int r = (int)rq * 4, k = (int)(i - rq * p.Kp);
+    if (r >= p.rows) return;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = k < p.cols ? p.src[(long long)(r + q) * p.ld + k] * p.scale : 0.f;
+      put16(p.dst, p.plane, (long long)(r + q) * p.ldo + k, v[q], p.planes);
+    }
+    put16x4(p.dst_t, p.plane_t, (long long)k * p.ldo_t + r, v, p.planes);
+    return;
+  }
+  const int per = p.Kp / 4;
+  const long long r = i / per;
+  const int k = 4 * (int)(i - r * per);
+  if (r >= p.rows) return;
+  const float* src = p.src + r * p.ld + k;
+  if (k + 4 <= p.cols && ((uintptr_t)src & 15) == 0) {
+    const f32x4_t x = *(const f32x4_t*)src;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = x[q] * p.scale;
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = k + q < p.cols ? src[q] * p.scale : 0.f;
+  }
+  put16x4(p.dst, p.plane, r * p.ldo + k, v, p.planes);
 }
 
 // Column sums of an fp32 [rows][ld] matrix over its first `rows` rows (ld a
@@ -398,14 +431,25 @@ __global__ __launch_bounds__(256) void k_split(SplitArgs p) {
 // lanes down the rows, whose sums are added in LDS.  One thread per column was a
 // serial chain of loads on 4 to 13 workgroups (236 us for 1024 rows, now 5 us).
 constexpr int kColsumCols = 16;
-__global__ __launch_bounds__(256) void k_colsum(const float* x, long long ld, int rows, int cols, float* out) {
+struct ColsumArgs {
+  const float* x[8];
+  float* out[8];
+  int ld[8], cols[8];
+  unsigned first[9];   // first workgroup of each layer
+  int n, rows;
+};
+__global__ __launch_bounds__(256) void k_colsum(ColsumArgs p) {
   __shared__ f32x4_t s_sum[64][4];
   const int q = threadIdx.x & 3, r0 = threadIdx.x >> 2;
-  const int c = blockIdx.x * kColsumCols + 4 * q;
+  int t = 0;
+  while (t + 1 < p.n && blockIdx.x >= p.first[t + 1]) ++t;
+  const float* x = p.x[t];
+  float* out = p.out[t];
+  const int ld = p.ld[t], cols = p.cols[t], c = (blockIdx.x - p.first[t]) * kColsumCols + 4 * q;
   f32x4_t s = {0.f, 0.f, 0.f, 0.f};
   if (c < cols)
 #pragma unroll 4
-    for (int r = r0; r < rows; r += 64) s += *(const f32x4_t*)(x + (long long)r * ld + c);
+    for (int r = r0; r < p.rows; r += 64) s += *(const f32x4_t*)(x + (long long)r * ld + c);
   s_sum[r0][q] = s;
   __syncthreads();
   for (int w = 32; w > 0; w >>= 1) {
@@ -425,45 +469,69 @@ __global__ __launch_bounds__(64) void k_loss_reduce(const double* part, int n, f
 }
 
 struct AdamArgs {
-  float* w;        // fp32 master [rows][cols]
+  float* w;        // fp32 master [rows][cols], rows a multiple of 4
   float* m;
   float* v;
   const float* g;
   uint16_t* wq;    // 16-bit planes [rows][cols]    (nullptr for biases)
   uint16_t* wqt;   // 16-bit planes [cols][rows]
   long long plane, plane_t;
-  int rows, cols, planes;
+  int rows, cols;
+};
+constexpr int kMaxSegments = 16;   // weights and biases of 8 layers
+struct AdamBatch {
+  AdamArgs t[kMaxSegments];
+  unsigned first[kMaxSegments + 1];   // first workgroup of each tensor
+  int n, planes;
   float lr, b1, b2, eps, c1, c2;   // c1 = 1/(1-b1^t), c2 = 1/(1-b2^t)
 };
 
-__global__ __launch_bounds__(256) void k_adam(AdamArgs p) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-  const long long total = (long long)p.rows * p.cols;
-  if (i >= total) return;
-  const float g = p.g[i];
-  const float m = p.b1 * p.m[i] + (1.f - p.b1) * g;
-  const float v = p.b2 * p.v[i] + (1.f - p.b2) * g * g;
-  p.m[i] = m;
-  p.v[i] = v;
-  const float w = p.w[i] - p.lr * (m * p.c1) / (sqrtf(v * p.c2) + p.eps);
-  p.w[i] = w;
-  if (p.wq) {
-    const int r = (int)(i / p.cols), c = (int)(i % p.cols);
-    put16(p.wq, p.plane, i, w, p.planes);
-    put16(p.wqt, p.plane_t, (long long)c * p.rows + r, w, p.planes);
+// All tensors in one launch (six for a three-layer network before).  A thread
+// takes four rows of a column, so that the transposed copy leaves in 8-byte
+// stores.  Bound by the 32 bytes per weight that the step moves.
+__global__ __launch_bounds__(256) void k_adam(AdamBatch b) {
+  int t = 0;
+  while (t + 1 < b.n && blockIdx.x >= b.first[t + 1]) ++t;
+  const AdamArgs& p = b.t[t];
+  const long long i = (long long)(blockIdx.x - b.first[t]) * 256 + threadIdx.x;
+  const int rq = (int)(i / p.cols), c = (int)(i - (long long)rq * p.cols);
+  if (4 * rq >= p.rows) return;
+  float w4[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const long long at = (long long)(4 * rq + q) * p.cols + c;
+    const float g = p.g[at];
+    const float m = b.b1 * p.m[at] + (1.f - b.b1) * g;
+    const float v = b.b2 * p.v[at] + (1.f - b.b2) * g * g;
+    p.m[at] = m;
+    p.v[at] = v;
+    const float w = p.w[at] - b.lr * (m * b.c1) / (sqrtf(v * b.c2) + b.eps);
+    p.w[at] = w;
+    w4[q] = w;
+    if (p.wq) put16(p.wq, p.plane, at, w, b.planes);
   }
+  if (p.wqt) put16x4(p.wqt, p.plane_t, (long long)c * p.rows + 4 * rq, w4, b.planes);
 }
 
-// params (packed, unpadded, W as [out][in]) <-> padded master copies
+// params (packed, unpadded, W as [out][in]) <-> padded master copies, all of them
+// in one launch
 struct ParamCopyArgs {
   const float* src;
   float* dst;
   int rows, cols, src_ld, dst_ld;
 };
-__global__ __launch_bounds__(256) void k_copy2d(ParamCopyArgs p) {
-  const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+struct ParamCopyBatch {
+  ParamCopyArgs t[kMaxSegments];
+  unsigned first[kMaxSegments + 1];
+  int n;
+};
+__global__ __launch_bounds__(256) void k_copy2d(ParamCopyBatch b) {
+  int t = 0;
+  while (t + 1 < b.n && blockIdx.x >= b.first[t + 1]) ++t;
+  const ParamCopyArgs& p = b.t[t];
+  const long long i = (long long)(blockIdx.x - b.first[t]) * 256 + threadIdx.x;
   if (i >= (long long)p.rows * p.cols) return;
-  const int r = (int)(i / p.cols), c = (int)(i % p.cols);
+  const int r = (int)(i / p.cols), c = (int)(i - (long long)r * p.cols);
   p.dst[(long long)r * p.dst_ld + c] = p.src[(long long)r * p.src_ld + c];
 }
 
@@ -568,11 +636,16 @@ int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
   return gemm_launch<1, EPI, 64>(a, st);
 }
 
-int split_launch(const float* src, long long ld, int rows, int cols, int Kp, uint16_t* dst, long long plane,
-                 long long ldo, int planes, int transpose, float scale, hipStream_t st) {
-  SplitArgs s{src, ld, dst, plane, ldo, rows, cols, Kp, planes, transpose, scale};
-  const long long total = (long long)rows * Kp;
-  hipLaunchKernelGGL(k_split, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, s);
+SplitArgs split_args(const float* src, long long ld, int rows, int cols, int Kp, uint16_t* dst, long long plane,
+                     long long ldo, int planes, float scale) {
+  SplitArgs s{src, ld, dst, plane, ldo, rows, cols, Kp, planes, scale, nullptr, 0, 0, 0};
+  s.wgs = (unsigned)(((long long)rows * (Kp / 4) + 255) / 256);
+  return s;
+}
+
+int split_launch(const SplitArgs& s0, const SplitArgs& s1, hipStream_t st) {
+  const SplitPair p{{s0, s1}};
+  hipLaunchKernelGGL(k_split, dim3(s0.wgs + s1.wgs), dim3(256), 0, st, p);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return mfail(PWFS_EHIP, "launch k_split: %s", hipGetErrorString(e));
   return PWFS_OK;
@@ -608,8 +681,9 @@ int gemm_run(const float* A, long long lda, const float* B, long long ldb, float
   uint16_t* b16 = (uint16_t*)((char*)ws + a256(2 * pl * (size_t)M * Kp));
   const long long ap = (long long)M * Kp, bp = (long long)N * Kp;
   int rc;
-  if ((rc = split_launch(A, lda, M, K, Kp, a16, ap, Kp, pl, 0, 1.f, st))) return rc;
-  if ((rc = split_launch(B, ldb, N, K, Kp, b16, bp, Kp, pl, 0, 1.f, st))) return rc;
+  if ((rc = split_launch(split_args(A, lda, M, K, Kp, a16, ap, Kp, pl, 1.f),
+                         split_args(B, ldb, N, K, Kp, b16, bp, Kp, pl, 1.f), st)))
+    return rc;
   GemmArgs g{};
   g.a = a16;
   g.b = b16;
@@ -855,22 +929,32 @@ extern "C" int pwfs_mlp_param_count(pwfs_mlp_t m, size_t* count) {
 
 namespace {
 
-int copy2d(const float* src, int src_ld, float* dst, int dst_ld, int rows, int cols, hipStream_t st) {
-  ParamCopyArgs a{src, dst, rows, cols, src_ld, dst_ld};
-  const long long total = (long long)rows * cols;
-  hipLaunchKernelGGL(k_copy2d, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, a);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return mfail(PWFS_EHIP, "launch k_copy2d: %s", hipGetErrorString(e));
-  return PWFS_OK;
-}
+// collects copies and issues them kMaxSegments at a time
+struct Copies {
+  ParamCopyBatch b{};
+  void add(const float* src, int src_ld, float* dst, int dst_ld, int rows, int cols) {
+    b.t[b.n] = {src, dst, rows, cols, src_ld, dst_ld};
+    b.first[b.n + 1] = b.first[b.n] + (unsigned)(((long long)rows * cols + 255) / 256);
+    ++b.n;
+  }
+  int launch(hipStream_t st) {
+    hipLaunchKernelGGL(k_copy2d, dim3(b.first[b.n]), dim3(256), 0, st, b);
+    b.n = 0;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return mfail(PWFS_EHIP, "launch k_copy2d: %s", hipGetErrorString(e));
+    return PWFS_OK;
+  }
+};
 
 // refresh the 16-bit weight copies from the fp32 masters (Adam with lr = 0
 // on zero moments would do the same; this is explicit)
 int refresh_q(pwfs_mlp_t m, int l, hipStream_t st) {
   const int rows = m->P[l + 1], cols = m->P[l];
-  int rc = split_launch(m->W[l], cols, rows, cols, cols, m->Wq[l], (long long)rows * cols, cols, m->planes, 0, 1.f, st);
-  if (rc) return rc;
-  return split_launch(m->W[l], cols, rows, cols, cols, m->Wqt[l], (long long)rows * cols, rows, m->planes, 1, 1.f, st);
+  SplitArgs a = split_args(m->W[l], cols, rows, cols, cols, m->Wq[l], (long long)rows * cols, cols, m->planes, 1.f);
+  a.dst_t = m->Wqt[l];
+  a.plane_t = (long long)rows * cols;
+  a.ldo_t = rows;
+  return split_launch(a, SplitArgs{}, st);
 }
 
 }  // namespace
@@ -880,12 +964,16 @@ extern "C" int pwfs_mlp_set_params(pwfs_mlp_t m, const float* params, void* stre
   hipStream_t st = (hipStream_t)stream;
   size_t off = 0;
   int rc;
+  Copies cp;
   for (int l = 0; l < m->L; ++l) {
     const int no = m->n[l + 1], ni = m->n[l];
-    if ((rc = copy2d(params + off, ni, m->W[l], m->P[l], no, ni, st))) return rc;
+    cp.add(params + off, ni, m->W[l], m->P[l], no, ni);
     off += (size_t)no * ni;
-    if ((rc = copy2d(params + off, no, m->b[l], no, 1, no, st))) return rc;
+    cp.add(params + off, no, m->b[l], no, 1, no);
     off += no;
+  }
+  if ((rc = cp.launch(st))) return rc;
+  for (int l = 0; l < m->L; ++l) {
     const size_t w = (size_t)m->P[l + 1] * m->P[l];
     if (hipMemsetAsync(m->mW[l], 0, 4 * w, st) != hipSuccess || hipMemsetAsync(m->vW[l], 0, 4 * w, st) != hipSuccess ||
         hipMemsetAsync(m->mb[l], 0, 4 * (size_t)m->P[l + 1], st) != hipSuccess ||
@@ -902,15 +990,15 @@ extern "C" int pwfs_mlp_get_params(pwfs_mlp_t m, float* params, void* stream) {
   if (!m || !params) return mfail(PWFS_EINVAL, "NULL argument");
   hipStream_t st = (hipStream_t)stream;
   size_t off = 0;
-  int rc;
+  Copies cp;
   for (int l = 0; l < m->L; ++l) {
     const int no = m->n[l + 1], ni = m->n[l];
-    if ((rc = copy2d(m->W[l], m->P[l], params + off, ni, no, ni, st))) return rc;
+    cp.add(m->W[l], m->P[l], params + off, ni, no, ni);
     off += (size_t)no * ni;
-    if ((rc = copy2d(m->b[l], no, params + off, no, 1, no, st))) return rc;
+    cp.add(m->b[l], no, params + off, no, 1, no);
     off += no;
   }
-  return PWFS_OK;
+  return cp.launch(st);
 }
 
 extern "C" int pwfs_mlp_set_linear(pwfs_mlp_t m, const float* C, void* stream) {
@@ -919,10 +1007,11 @@ extern "C" int pwfs_mlp_set_linear(pwfs_mlp_t m, const float* C, void* stream) {
     m->have_linear = false;
     return PWFS_OK;
   }
-  int rc;
   const int no = m->n[m->L], ni = m->n[0];
   // rows and columns past the true sizes stay zero (the workspace is cleared at create)
-  if ((rc = copy2d(C, ni, m->C, m->P[0], no, ni, (hipStream_t)stream))) return rc;
+  Copies cp;
+  cp.add(C, ni, m->C, m->P[0], no, ni);
+  if (const int rc = cp.launch((hipStream_t)stream)) return rc;
   m->have_linear = true;
   m->c_scale = 0.f;
   return PWFS_OK;
@@ -937,13 +1026,15 @@ extern "C" int pwfs_mlp_get_state(pwfs_mlp_t m, float* moments, long long* step,
   int rc;
   for (int which = 0; which < 2; ++which) {
     size_t off = which * count;
+    Copies cp;
     for (int l = 0; l < m->L; ++l) {
       const int no = m->n[l + 1], ni = m->n[l];
-      if ((rc = copy2d(which ? m->vW[l] : m->mW[l], m->P[l], moments + off, ni, no, ni, st))) return rc;
+      cp.add(which ? m->vW[l] : m->mW[l], m->P[l], moments + off, ni, no, ni);
       off += (size_t)no * ni;
-      if ((rc = copy2d(which ? m->vb[l] : m->mb[l], no, moments + off, no, 1, no, st))) return rc;
+      cp.add(which ? m->vb[l] : m->mb[l], no, moments + off, no, 1, no);
       off += no;
     }
+    if ((rc = cp.launch(st))) return rc;
   }
   *step = m->step;
   return PWFS_OK;
@@ -958,13 +1049,15 @@ extern "C" int pwfs_mlp_set_state(pwfs_mlp_t m, const float* moments, long long 
   int rc;
   for (int which = 0; which < 2; ++which) {
     size_t off = which * count;
+    Copies cp;
     for (int l = 0; l < m->L; ++l) {
       const int no = m->n[l + 1], ni = m->n[l];
-      if ((rc = copy2d(moments + off, ni, which ? m->vW[l] : m->mW[l], m->P[l], no, ni, st))) return rc;
+      cp.add(moments + off, ni, which ? m->vW[l] : m->mW[l], m->P[l], no, ni);
       off += (size_t)no * ni;
-      if ((rc = copy2d(moments + off, no, which ? m->vb[l] : m->mb[l], no, 1, no, st))) return rc;
+      cp.add(moments + off, no, which ? m->vb[l] : m->mb[l], no, 1, no);
       off += no;
     }
+    if ((rc = cp.launch(st))) return rc;
   }
   m->step = step;
   return PWFS_OK;
@@ -980,9 +1073,13 @@ int mlp_forward(pwfs_mlp_t m, const float* x, int batch, float* y, float out_sca
   int rc;
   // input activations (and their transpose, used by dW of layer 0)
   const long long a0 = (long long)m->Bm * m->P[0];
-  if ((rc = split_launch(x, m->n[0], batch, m->n[0], m->P[0], m->H[0], a0, m->P[0], pl, 0, 1.f, st))) return rc;
-  if (target)
-    if ((rc = split_launch(x, m->n[0], batch, m->n[0], m->P[0], m->Ht[0], a0, m->Bm, pl, 1, 1.f, st))) return rc;
+  SplitArgs xs = split_args(x, m->n[0], batch, m->n[0], m->P[0], m->H[0], a0, m->P[0], pl, 1.f);
+  if (target) {   // batch is a multiple of 32
+    xs.dst_t = m->Ht[0];
+    xs.plane_t = a0;
+    xs.ldo_t = m->Bm;
+  }
+  if ((rc = split_launch(xs, SplitArgs{}, st))) return rc;
   for (int l = 0; l < L; ++l) {
     GemmArgs g{};
     g.a = m->H[l];
@@ -1016,7 +1113,8 @@ int mlp_forward(pwfs_mlp_t m, const float* x, int batch, float* y, float out_sca
         // C / out_scale extend K after the layer's own weights
         if (m->c_scale != out_scale) {
           const int PL = m->P[L], P0 = m->P[0];
-          if ((rc = split_launch(m->C, P0, PL, P0, P0, m->Cq, (long long)PL * P0, P0, pl, 0, 1.f / out_scale, st)))
+          if ((rc = split_launch(
+                   split_args(m->C, P0, PL, P0, P0, m->Cq, (long long)PL * P0, P0, pl, 1.f / out_scale), SplitArgs{}, st)))
             return rc;
           m->c_scale = out_scale;
         }
@@ -1075,6 +1173,8 @@ extern "C" int pwfs_mlp_grad(pwfs_mlp_t m, const float* x, const float* t, int b
                        1.f / ((float)batch * (float)m->n[L]), loss);
     if (hipGetLastError() != hipSuccess) return mfail(PWFS_EHIP, "launch k_loss_reduce");
   }
+  ColsumArgs cs{};   // bias gradients of all layers, after the last product
+  cs.rows = batch;
   for (int l = L - 1; l >= 0; --l) {
     // dW_l = G_{l+1}^T H_l : A = Gt_{l+1} [n_{l+1}][batch], B = Ht_l [P_l][batch], K = batch
     GemmArgs g{};
@@ -1091,9 +1191,12 @@ extern "C" int pwfs_mlp_grad(pwfs_mlp_t m, const float* x, const float* t, int b
     g.c = m->gW[l];
     g.ldc = m->P[l];
     if ((rc = gemm_dispatch<E_STORE>(pl, g, st))) return rc;
-    hipLaunchKernelGGL(k_colsum, dim3((unsigned)((m->n[l + 1] + kColsumCols - 1) / kColsumCols)), dim3(256), 0, st,
-                       m->dZ[l + 1], (long long)m->P[l + 1], batch, m->n[l + 1], m->gb[l]);
-    if (hipGetLastError() != hipSuccess) return mfail(PWFS_EHIP, "launch k_colsum");
+    cs.x[cs.n] = m->dZ[l + 1];
+    cs.out[cs.n] = m->gb[l];
+    cs.ld[cs.n] = m->P[l + 1];
+    cs.cols[cs.n] = m->n[l + 1];
+    cs.first[cs.n + 1] = cs.first[cs.n] + (unsigned)((m->n[l + 1] + kColsumCols - 1) / kColsumCols);
+    ++cs.n;
     if (l == 0) break;
     // G_l = (G_{l+1} W_l) * gelu'(Z_l) : A = G_{l+1} [batch][P_{l+1}], B = Wqt_l [P_l][P_{l+1}]
     GemmArgs d{};
@@ -1119,16 +1222,20 @@ extern "C" int pwfs_mlp_grad(pwfs_mlp_t m, const float* x, const float* t, int b
     d.planes_out = pl;
     if ((rc = gemm_dispatch<E_DHIDDEN>(pl, d, st))) return rc;
   }
+  hipLaunchKernelGGL(k_colsum, dim3(cs.first[cs.n]), dim3(256), 0, st, cs);
+  if (hipGetLastError() != hipSuccess) return mfail(PWFS_EHIP, "launch k_colsum");
   m->have_grad = true;
   if (grads) {
     size_t off = 0;
+    Copies cp;
     for (int l = 0; l < L; ++l) {
       const int no = m->n[l + 1], ni = m->n[l];
-      if ((rc = copy2d(m->gW[l], m->P[l], grads + off, ni, no, ni, st))) return rc;
+      cp.add(m->gW[l], m->P[l], grads + off, ni, no, ni);
       off += (size_t)no * ni;
-      if ((rc = copy2d(m->gb[l], no, grads + off, no, 1, no, st))) return rc;
+      cp.add(m->gb[l], no, grads + off, no, 1, no);
       off += no;
     }
+    if ((rc = cp.launch(st))) return rc;
   }
   return PWFS_OK;
 }
@@ -1142,17 +1249,27 @@ extern "C" int pwfs_mlp_adam(pwfs_mlp_t m, float lr, float beta1, float beta2, f
   m->step += 1;
   const float c1 = (float)(1.0 / (1.0 - std::pow((double)beta1, m->step)));
   const float c2 = (float)(1.0 / (1.0 - std::pow((double)beta2, m->step)));
+  AdamBatch b{};
+  b.planes = m->planes;
+  b.lr = lr;
+  b.b1 = beta1;
+  b.b2 = beta2;
+  b.eps = eps;
+  b.c1 = c1;
+  b.c2 = c2;
+  auto add = [&](const AdamArgs& a) {
+    b.t[b.n] = a;
+    b.first[b.n + 1] = b.first[b.n] + (unsigned)(((long long)(a.rows / 4) * a.cols + 255) / 256);
+    ++b.n;
+  };
   for (int l = 0; l < m->L; ++l) {
     const int rows = m->P[l + 1], cols = m->P[l];
-    AdamArgs a{m->W[l], m->mW[l], m->vW[l], m->gW[l], m->Wq[l], m->Wqt[l], (long long)rows * cols,
-               (long long)rows * cols, rows, cols, m->planes, lr, beta1, beta2, eps, c1, c2};
-    const long long tw = (long long)rows * cols;
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)((tw + 255) / 256)), dim3(256), 0, st, a);
-    AdamArgs ab{m->b[l], m->mb[l], m->vb[l], m->gb[l], nullptr, nullptr, 0, 0, 1, rows, m->planes,
-                lr, beta1, beta2, eps, c1, c2};
-    hipLaunchKernelGGL(k_adam, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, st, ab);
-    if (hipGetLastError() != hipSuccess) return mfail(PWFS_EHIP, "launch k_adam");
+    const long long w = (long long)rows * cols;
+    add({m->W[l], m->mW[l], m->vW[l], m->gW[l], m->Wq[l], m->Wqt[l], w, w, rows, cols});
+    add({m->b[l], m->mb[l], m->vb[l], m->gb[l], nullptr, nullptr, 0, 0, rows, 1});
   }
+  hipLaunchKernelGGL(k_adam, dim3(b.first[b.n]), dim3(256), 0, st, b);
+  if (hipGetLastError() != hipSuccess) return mfail(PWFS_EHIP, "launch k_adam");
   return PWFS_OK;
 }
 
