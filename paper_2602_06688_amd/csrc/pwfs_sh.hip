@@ -12,9 +12,15 @@
 // W[u][x] = exp(-2 pi i (u - M/2 + 1/2)(x - (b-1)/2) / M) puts the focal
 // samples at half-integer frequencies (a flat wavefront's spot sits on the
 // corner of the four central samples).  A 2-D DFT of a b x b block onto
-// M x M samples as two small products costs 2 b M (b + M) real multiply-adds
-// (per complex term 4): for b << M (8 vs 56, 7 vs 240) that is less than a
-// zero-padded M-point FFT, and it needs no radix plan for M = 56 or 240.
+// M x M samples as two small products needs no radix plan for M = 56 or 240.
+//
+// Both indices of W = c + i s are centred, so W[u][b-1-x] = W[M-1-u][x] =
+// conj W[u][x].  With E+- = E(x) +- E(b-1-x), x < h = ceil(b / 2) (a middle
+// element enters E+ once and E- as zero),
+//   T[u] = C + i S,  T[M-1-u] = C - i S,  C = sum E+ c,  S = sum E- s,
+// half the terms, each a complex number times a real one, and two samples from
+// one pair of sums: 2 b real multiply-adds per two samples instead of 8 b.  The
+// same holds for F along v, with T folded along y as it is stored.
 //
 // Polychromatic sensor (Table 4: PolyChromSH): the workgroup runs the three
 // steps once per sampled wavelength lambda_l, with that wavelength's phase and
@@ -54,7 +60,7 @@ int sfail(int code, const char* fmt, ...) {
 struct ShArgs {
   const float* opd;        // [frames][D][D]
   const float* amp;        // [D][D]
-  const float2* W;         // [n_lam][M][b]
+  const float2* W;         // [n_lam][ceil(M / 2)][ceil(b / 2)]
   const uint8_t* valid;    // [n][n]
   float* pixels;           // [frames][n][n][k][k] or nullptr
   float* slopes;           // [frames][2][n][n]
@@ -63,85 +69,42 @@ struct ShArgs {
   double two_pi_over_lam[PWFS_MAX_LAMBDA];
 };
 
-// Row stride (in complex values) of the DFT table W [M][b] in LDS: an even
-// b is padded by one, so that the rows that a wavefront's lanes read
-// together (consecutive u in the T product, the rows v of a pixel's samples)
-// start on different banks; with b = 8 unpadded rows are 16 words apart and
-// eight of them share two banks of 32.
-__host__ __device__ constexpr int sw_stride(int b) { return (b % 2 == 0) ? b + 1 : b; }
+// Folded sizes: h = ceil(b / 2) samples, ceil(M / 2) frequencies.  The rows of
+// the (c, s) table in LDS have an odd stride, so that the rows that consecutive
+// lanes read in the T product start on different banks.
+__host__ __device__ constexpr int sh_half(int n) { return (n + 1) / 2; }
+__host__ __device__ constexpr int sc_stride(int h) { return h | 1; }
 
-// Row stride (in complex values) of the row products T [b][M] in LDS: 257
-// for M <= 256, fixed at compile time, so that the loads of a column of T
-// in the pixel loop take their row offsets as immediates (one LDS load and
-// no address arithmetic per term).  2056 bytes is beyond the reach of both
-// paired-load forms (whose two rows collided on banks: a stride that is a
-// multiple of 512 bytes puts both on one bank), and consecutive rows start
-// two banks apart.  M above 256 keeps M.
-constexpr int kTFixed = 256, kTStride = 257;
-__host__ __device__ constexpr int t_stride(int M) { return M <= kTFixed ? kTStride : M; }
-
-// Pixel sum of thread s of a pixel whose focal block starts at row pr r and
-// column pc r: |sum_y W[v][y] T[y][u]|^2 over every row v of the block and
-// the columns u = s, s + tpp, ... of it, NC columns at a time.  Their T
-// columns stay in registers while the block's W rows stream past, so each W
-// value read from LDS (the lanes of one pixel row read the same one) serves
-// NC samples.  Columns past the block are zero (their loads re-read a valid
-// column), so they add exact zeros.
-template <int BB, int NC>
-__device__ __forceinline__ float sh_pixel_cols(const float2* sW, const float2* sT, int ts, int r, int tpp, int s,
-                                               int pr, int pc) {
-  constexpr int BW = sw_stride(BB);
-  float acc = 0.f;
-  for (int u0 = s; u0 < r; u0 += NC * tpp) {
-    float2 tc[NC][BB];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const bool in = u0 + c * tpp < r;
-      const int u = pc * r + (in ? u0 + c * tpp : u0);
-#pragma unroll
-      for (int y = 0; y < BB; ++y) tc[c][y] = in ? sT[y * ts + u] : make_float2(0.f, 0.f);
-    }
-    for (int vv = 0; vv < r; ++vv) {
-      const float2* wrow = sW + (pr * r + vv) * BW;
-      float re[NC], im[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) re[c] = im[c] = 0.f;
-#pragma unroll
-      for (int y = 0; y < BB; ++y) {
-        const float2 w = wrow[y];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          re[c] = fmaf(w.x, tc[c][y].x, fmaf(-w.y, tc[c][y].y, re[c]));
-          im[c] = fmaf(w.x, tc[c][y].y, fmaf(w.y, tc[c][y].x, im[c]));
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c) acc = fmaf(re[c], re[c], fmaf(im[c], im[c], acc));
-    }
-  }
-  return acc;
-}
-
-// Threads per pixel in the pixel loop: the largest power of two that keeps
-// the workgroup's kShBlock threads busy without exceeding r.
-__host__ __device__ inline int sh_tpp(int kk, int r) {
+// Threads per pair of pixels (pr, pc), (k-1-pr, pc) in the pixel loop: the
+// largest power of two that keeps kShBlock threads busy without exceeding r.
+__host__ __device__ inline int sh_tpp(int pairs, int r) {
   int tpp = 1;
-  while (tpp * 2 * kk <= kShBlock && tpp * 2 <= r) tpp *= 2;
+  while (tpp * 2 * pairs <= kShBlock && tpp * 2 <= r) tpp *= 2;
   return tpp;
 }
 
-// BB: the subaperture width b at compile time (the pixel loop then keeps NC
-// columns of T in registers, sh_pixel_cols), 0 for a run-time b.  FIXT: M <=
-// 256, T stored at the fixed stride kTStride.  NC = 4 needs a thread to own at
-// least four columns (r >= 4 tpp) to pay for its registers; the host picks it
-// then, for b <= 8.
-template <int BB, bool FIXT, int NC>
-__global__ __launch_bounds__(kShBlock) void k_sh(ShArgs p) {
-  extern __shared__ float2 sh_mem[];
+size_t sh_lds(int b, int M, int k, int nt) {
+  const size_t h = sh_half(b);
+  return sizeof(float4) * (h * M + 2 * h * h) + sizeof(float2) * ((size_t)sh_half(M) * sc_stride((int)h) + (size_t)b * b) +
+         sizeof(float) * ((size_t)k * k + 1 + 2 * nt);
+}
+
+// H: the folded subaperture width at compile time.  A thread of a pixel pair
+// keeps NC focal columns of the folded T in registers while the pair's table
+// rows stream past (the lanes of one pixel row read the same ones), so a row read
+// from LDS serves 2 NC samples.  NC = 4 pays where a thread owns at least four
+// columns (r >= 4 tpp), for H <= 4.  NT = 128 where the pairs fill no more (the
+// 8 x 8 pixels of 56 samples).  Bound by vector issue: 4 H + 8 instructions per
+// two samples, where the unfolded complex products took 8 b + 4.  68 x 68
+// subapertures of 7 pixels onto 240 x 240, 10 frames: 1298 -> 524 us; 20 x 20 of
+// 8 pixels onto 56 x 56, 500 frames: 655 -> 331 us.
+template <int H, int NC, int NT>
+__global__ __launch_bounds__(NT) void k_sh(ShArgs p) {
+  extern __shared__ float4 sh_mem[];
   const int tid = threadIdx.x;
   const int sub = blockIdx.x % (p.n * p.n), f = blockIdx.x / (p.n * p.n);
   const int si = sub / p.n, sj = sub % p.n;
-  const int b = p.b, M = p.M, r = p.r, k = p.k;
+  const int b = p.b, M = p.M, r = p.r, k = p.k, hm = sh_half(M);
   const int kk = k * k;
   float* pix_out = p.pixels ? p.pixels + ((size_t)f * p.n * p.n + sub) * kk : nullptr;
   float* sl = p.slopes + (size_t)f * 2 * p.n * p.n;
@@ -151,24 +114,23 @@ __global__ __launch_bounds__(kShBlock) void k_sh(ShArgs p) {
       sl[p.n * p.n + sub] = 0.f;
     }
     if (pix_out)
-      for (int i = tid; i < kk; i += kShBlock) pix_out[i] = 0.f;
+      for (int i = tid; i < kk; i += NT) pix_out[i] = 0.f;
     return;
   }
-  constexpr int BW = BB > 0 ? sw_stride(BB) : 0;
-  const int bw = BB > 0 ? BW : sw_stride(b);
-  float2* sW = sh_mem;                 // [M][bw], row u holds W[u][0 .. b)
-  float2* sE = sW + M * bw;            // [b][b]
-  const int ts = FIXT ? kTStride : M;   // T row stride (t_stride(M))
-  float2* sT = sE + b * b;             // [b][ts], row y holds T[y][0 .. M)
-  float* sP = (float*)(sT + b * ts);   // [kk] pixel values, then [kShBlock] partials
-  float* sR = sP + kk;
+  constexpr int CW = sc_stride(H);
+  float4* sT = sh_mem;                       // [H][M]: T+ (re, im), T- (re, im) of rows y, b-1-y
+  float4* sF = sT + H * M;                   // [H][H][2]: E folded along y (+, -); each (x+ re, im, x- re, im)
+  float2* sC = (float2*)(sF + 2 * H * H);    // [hm][CW] (c, s)
+  float2* sE = sC + hm * CW;                 // [b][b]
+  float* sP = (float*)(sE + b * b);          // [kk] pixel values
+  float2* sR = (float2*)(sP + (kk + 1) / 2 * 2);   // [NT] partial sums of a pair
 
   const float* opd = p.opd + (size_t)f * p.D * p.D;
-  // one pass per wavelength; the pixel loop's last barrier frees sW, sE and
-  // sT for the next one
+  // one pass per wavelength; the pixel loop's last barrier frees the LDS for the
+  // next one
   for (int l = 0; l < p.n_lam; ++l) {
-    for (int i = tid; i < M * b; i += kShBlock) sW[(i / b) * bw + i % b] = p.W[(size_t)l * M * b + i];
-    for (int i = tid; i < b * b; i += kShBlock) {
+    for (int i = tid; i < hm * H; i += NT) sC[(i / H) * CW + i % H] = p.W[(size_t)l * hm * H + i];
+    for (int i = tid; i < b * b; i += NT) {
       const int y = i / b, x = i % b;
       const size_t g = (size_t)(si * b + y) * p.D + sj * b + x;
       const double ph = (double)opd[g] * p.two_pi_over_lam[l];
@@ -180,53 +142,113 @@ __global__ __launch_bounds__(kShBlock) void k_sh(ShArgs p) {
       sE[i] = make_float2(a * cs, a * sn);
     }
     __syncthreads();
-    // T[y][u] = sum_x E[y][x] W[u][x]
-    for (int i = tid; i < b * M; i += kShBlock) {
-      const int y = i / M, u = i % M;
-      float re = 0.f, im = 0.f;
-      for (int x = 0; x < b; ++x) {
-        const float2 e = sE[y * b + x], w = sW[u * bw + x];
-        re = fmaf(e.x, w.x, fmaf(-e.y, w.y, re));
-        im = fmaf(e.x, w.y, fmaf(e.y, w.x, im));
-      }
-      sT[y * ts + u] = make_float2(re, im);
+    for (int i = tid; i < H * H; i += NT) {
+      const int y = i / H, x = i % H, yb = b - 1 - y, xb = b - 1 - x;
+      const float2 e00 = sE[y * b + x];
+      const float2 z = make_float2(0.f, 0.f);
+      const float2 e01 = xb != x ? sE[y * b + xb] : z;
+      const float2 e10 = yb != y ? sE[yb * b + x] : z;
+      const float2 e11 = xb != x && yb != y ? sE[yb * b + xb] : z;
+      // along x: the middle element is E+ itself, and no E-
+      const bool mx = xb == x, my = yb == y;
+      const float2 p0 = make_float2(e00.x + e01.x, e00.y + e01.y), p1 = make_float2(e10.x + e11.x, e10.y + e11.y);
+      const float2 m0 = mx ? z : make_float2(e00.x - e01.x, e00.y - e01.y);
+      const float2 m1 = mx ? z : make_float2(e10.x - e11.x, e10.y - e11.y);
+      sF[2 * i] = make_float4(p0.x + p1.x, p0.y + p1.y, m0.x + m1.x, m0.y + m1.y);
+      // 0 x: a sample that is not finite stays in the row's both folds
+      sF[2 * i + 1] = my ? make_float4(0.f * p0.x, 0.f * p0.y, 0.f * m0.x, 0.f * m0.y)
+                         : make_float4(p0.x - p1.x, p0.y - p1.y, m0.x - m1.x, m0.y - m1.y);
     }
     __syncthreads();
-    // pixels: TPP threads per pixel share its r x r focal samples (fixed order).
-    // With b known at compile time thread s takes the focal columns s, s + TPP,
-    // ... (sh_pixel_cols); otherwise the rows s, s + TPP, ... one W row at a
-    // time.
-    const int tpp = sh_tpp(kk, r);
-    for (int base = 0; base < kk * tpp; base += kShBlock) {
+    // T+-[y][u], T+-[y][M-1-u]
+    for (int i = tid; i < H * hm; i += NT) {
+      const int y = i / hm, u = i - y * hm;
+      const float2* w = sC + u * CW;
+      const float4* e = sF + 2 * H * y;
+      float cr = 0.f, ci = 0.f, sr = 0.f, sii = 0.f, dr = 0.f, di = 0.f, tr = 0.f, ti = 0.f;
+#pragma unroll
+      for (int x = 0; x < H; ++x) {
+        const float2 cs = w[x];
+        const float4 a = e[2 * x], d = e[2 * x + 1];
+        cr = fmaf(a.x, cs.x, cr);
+        ci = fmaf(a.y, cs.x, ci);
+        sr = fmaf(a.z, cs.y, sr);
+        sii = fmaf(a.w, cs.y, sii);
+        dr = fmaf(d.x, cs.x, dr);
+        di = fmaf(d.y, cs.x, di);
+        tr = fmaf(d.z, cs.y, tr);
+        ti = fmaf(d.w, cs.y, ti);
+      }
+      // C + i S and C - i S
+      sT[y * M + u] = make_float4(cr - sii, ci + sr, dr - ti, di + tr);
+      sT[y * M + M - 1 - u] = make_float4(cr + sii, ci - sr, dr + ti, di - tr);
+    }
+    __syncthreads();
+    // pixels: tpp threads per pixel pair share its focal columns s, s + tpp, ...
+    // (fixed order).  The two pixels' rows v and M-1-v come from one pair of
+    // sums; with k odd the middle pixel row is its own pair, over half its rows,
+    // and the middle v of an odd M is its own mirror image.
+    const int pairs = sh_half(k) * k;
+    const int tpp = sh_tpp(pairs, r);
+    for (int base = 0; base < pairs * tpp; base += NT) {
       const int slot = base + tid;
-      const int P = slot / tpp, s = slot % tpp;
-      float acc = 0.f;
-      if (P < kk) {
-        const int pr = P / k, pc = P % k;
-        if constexpr (BB > 0) {
-          acc = sh_pixel_cols<BB, NC>(sW, sT, ts, r, tpp, s, pr, pc);
-        } else {
-          for (int vv = s; vv < r; vv += tpp) {
-            const int v = pr * r + vv;
-            for (int uu = 0; uu < r; ++uu) {
-              const int u = pc * r + uu;
-              float re = 0.f, im = 0.f;
-              for (int y = 0; y < b; ++y) {
-                const float2 w = sW[v * bw + y], t = sT[y * ts + u];
-                re = fmaf(w.x, t.x, fmaf(-w.y, t.y, re));
-                im = fmaf(w.x, t.y, fmaf(w.y, t.x, im));
-              }
-              acc = fmaf(re, re, fmaf(im, im, acc));
-            }
+      const int P = slot / tpp, s = slot - P * tpp;
+      const int pr = P / k, pc = P - pr * k;
+      const bool mid = 2 * pr == k - 1;
+      float acc1 = 0.f, acc2 = 0.f;
+      if (P < pairs) {
+        const int rows = mid ? r / 2 : r;
+        for (int u0 = s; u0 < r; u0 += NC * tpp) {
+          float4 tc[NC][H];
+#pragma unroll
+          for (int c = 0; c < NC; ++c) {
+            const bool in = u0 + c * tpp < r;
+            const int u = pc * r + (in ? u0 + c * tpp : u0);
+#pragma unroll
+            for (int y = 0; y < H; ++y) tc[c][y] = in ? sT[y * M + u] : make_float4(0.f, 0.f, 0.f, 0.f);
           }
+          auto row = [&](int v, bool both) {
+            const float2* w = sC + v * CW;
+            float cr[NC], ci[NC], sr[NC], sii[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) cr[c] = ci[c] = sr[c] = sii[c] = 0.f;
+#pragma unroll
+            for (int y = 0; y < H; ++y) {
+              const float2 cs = w[y];
+#pragma unroll
+              for (int c = 0; c < NC; ++c) {
+                cr[c] = fmaf(cs.x, tc[c][y].x, cr[c]);
+                ci[c] = fmaf(cs.x, tc[c][y].y, ci[c]);
+                sr[c] = fmaf(cs.y, tc[c][y].z, sr[c]);
+                sii[c] = fmaf(cs.y, tc[c][y].w, sii[c]);
+              }
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+              const float ar = cr[c] - sii[c], ai = ci[c] + sr[c];
+              acc1 = fmaf(ar, ar, fmaf(ai, ai, acc1));
+              if (both) {
+                const float br = cr[c] + sii[c], bi = ci[c] - sr[c];
+                acc2 = fmaf(br, br, fmaf(bi, bi, acc2));
+              }
+            }
+          };
+          for (int vv = 0; vv < rows; ++vv) row(pr * r + vv, true);
+          if (mid && (r & 1)) row(pr * r + rows, false);
         }
       }
-      sR[tid] = acc;
+      sR[tid] = make_float2(acc1, acc2);
       __syncthreads();
-      if (s == 0 && P < kk) {
-        float v = sR[tid];
-        for (int q = 1; q < tpp; ++q) v += sR[tid + q];
-        sP[P] = (l == 0 ? 0.f : sP[P]) + v * p.wnorm[l];
+      if (s == 0 && P < pairs) {
+        float2 v = sR[tid];
+        for (int q = 1; q < tpp; ++q) {
+          v.x += sR[tid + q].x;
+          v.y += sR[tid + q].y;
+        }
+        if (mid) v.x += v.y;
+        const int P2 = (k - 1 - pr) * k + pc;
+        sP[P] = (l == 0 ? 0.f : sP[P]) + v.x * p.wnorm[l];
+        if (!mid) sP[P2] = (l == 0 ? 0.f : sP[P2]) + v.y * p.wnorm[l];
       }
       __syncthreads();
     }
@@ -255,6 +277,19 @@ __global__ __launch_bounds__(kShBlock) void k_sh(ShArgs p) {
   }
 }
 
+// calls fn(kernel, threads) with the kernel of a folded width, for a thread that
+// owns `cols` columns of a pixel
+template <int H, class Fn>
+void sh_pick(int h, int cols, bool narrow, Fn fn) {
+  if constexpr (H <= 16) {
+    if (h != H) return sh_pick<H + 1>(h, cols, narrow, fn);
+    constexpr int NC = H <= 8 ? 2 : 1;
+    if constexpr (H <= 4)
+      if (cols >= 4) return narrow ? fn(k_sh<H, 4, 128>, 128) : fn(k_sh<H, 4, kShBlock>, kShBlock);
+    return narrow ? fn(k_sh<H, NC, 128>, 128) : fn(k_sh<H, NC, kShBlock>, kShBlock);
+  }
+}
+
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace
@@ -271,6 +306,8 @@ struct pwfs_sh_s {
   float2* W = nullptr;
   uint8_t* valid = nullptr;
   size_t lds = 0;
+  bool narrow = false;   // 128 threads
+  int cols = 1;          // focal columns of a pixel per thread
 };
 
 extern "C" int pwfs_sh_validate(const pwfs_sh_desc* d) {
@@ -297,7 +334,9 @@ extern "C" int pwfs_sh_validate(const pwfs_sh_desc* d) {
     if (std::fabs(wsum - 1.0) > 1e-9) return sfail(PWFS_EINVAL, "lambda_weights must sum to 1");
   }
   const int k = d->n_fft / d->rebin;
-  const size_t lds = sizeof(float2) * ((size_t)d->n_fft * sw_stride(b) + (size_t)b * t_stride(d->n_fft) + (size_t)b * b) +
+  // the size of the unfolded tables, which the folded ones stay below
+  const size_t wide = (size_t)(b % 2 == 0 ? b + 1 : b), tall = (size_t)(d->n_fft <= 256 ? 257 : d->n_fft);
+  const size_t lds = sizeof(float2) * ((size_t)d->n_fft * wide + (size_t)b * tall + (size_t)b * b) +
                      sizeof(float) * ((size_t)k * k + kShBlock);
   if (lds > 150 * 1024) return sfail(PWFS_EUNSUPPORTED, "subaperture tables exceed the LDS (n_fft x b too large)");
   return PWFS_OK;
@@ -345,7 +384,8 @@ extern "C" int pwfs_sh_plan(const pwfs_sh_desc* d, int max_frames, void* ws, siz
   if (nv == 0) return sfail(PWFS_EINVAL, "no valid subaperture");
   // per wavelength: W_l[u][x] with the frequency scale s_l = lambda_ref / lambda_l
   const int nl = d->n_lambda >= 2 ? d->n_lambda : 1;
-  std::vector<float2> W((size_t)nl * M * b);
+  const int hm = sh_half(M), hb = sh_half(b);   // the other entries are conjugates
+  std::vector<float2> W((size_t)nl * hm * hb);
   std::vector<double> scale(nl, 1.0), lam(nl, d->lambda_nm), wgt(nl, 1.0);
   for (int l = 0; l < nl && d->n_lambda >= 2; ++l) {
     lam[l] = d->lambdas_nm[l];
@@ -353,10 +393,10 @@ extern "C" int pwfs_sh_plan(const pwfs_sh_desc* d, int max_frames, void* ws, siz
     scale[l] = d->lambda_nm / d->lambdas_nm[l];
   }
   for (int l = 0; l < nl; ++l)
-    for (int u = 0; u < M; ++u)
-      for (int x = 0; x < b; ++x) {
+    for (int u = 0; u < hm; ++u)
+      for (int x = 0; x < hb; ++x) {
         const double a = -2.0 * kPiSh * (u - M / 2.0 + 0.5) * (x - (b - 1) / 2.0) * scale[l] / M;
-        W[((size_t)l * M + u) * b + x] = make_float2((float)std::cos(a), (float)std::sin(a));
+        W[((size_t)l * hm + u) * hb + x] = make_float2((float)std::cos(a), (float)std::sin(a));
       }
   pwfs_sh_s* s = new (std::nothrow) pwfs_sh_s();
   if (!s) return sfail(PWFS_EINVAL, "out of host memory");
@@ -380,8 +420,10 @@ extern "C" int pwfs_sh_plan(const pwfs_sh_desc* d, int max_frames, void* ws, siz
   s->W = (float2*)p;
   p += a256(sizeof(float2) * nl * M * b);
   s->valid = (uint8_t*)p;
-  s->lds = sizeof(float2) * ((size_t)M * sw_stride(b) + (size_t)b * t_stride(M) + (size_t)b * b) +
-           sizeof(float) * ((size_t)s->k * s->k + kShBlock);
+  const int pairs = sh_half(s->k) * s->k, tpp = sh_tpp(pairs, s->r);
+  s->narrow = pairs * tpp <= 128;
+  s->cols = s->r / tpp;
+  s->lds = sh_lds(b, M, s->k, s->narrow ? 128 : kShBlock);
   hipStream_t st = (hipStream_t)stream;
   if (hipMemcpyAsync(s->amp, A.data(), A.size() * sizeof(float), hipMemcpyHostToDevice, st) != hipSuccess ||
       hipMemcpyAsync(s->W, W.data(), W.size() * sizeof(float2), hipMemcpyHostToDevice, st) != hipSuccess ||
@@ -390,36 +432,13 @@ extern "C" int pwfs_sh_plan(const pwfs_sh_desc* d, int max_frames, void* ws, siz
     delete s;
     return sfail(PWFS_EHIP, "uploading the sensor tables failed");
   }
-  static bool lds_set = false;
-  if (!lds_set) {
-    const void* fns[] = {
-        (const void*)k_sh<0, true, 2>,  (const void*)k_sh<4, true, 2>,  (const void*)k_sh<7, true, 2>,
-        (const void*)k_sh<8, true, 2>,  (const void*)k_sh<16, true, 2>, (const void*)k_sh<0, false, 2>,
-        (const void*)k_sh<4, false, 2>, (const void*)k_sh<7, false, 2>, (const void*)k_sh<8, false, 2>,
-        (const void*)k_sh<16, false, 2>, (const void*)k_sh<4, true, 4>, (const void*)k_sh<7, true, 4>,
-        (const void*)k_sh<8, true, 4>,  (const void*)k_sh<4, false, 4>, (const void*)k_sh<7, false, 4>,
-        (const void*)k_sh<8, false, 4>};
-    for (const void* fn : fns)
-      if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-        (void)hipGetLastError();
-    lds_set = true;
-  }
+  sh_pick<1>(hb, s->cols, s->narrow, [](void (*fn)(ShArgs), int) {
+    if (hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
+      (void)hipGetLastError();
+  });
   *out = s;
   return PWFS_OK;
 }
-
-namespace {
-template <int BB, bool FIXT>
-void launch_sh(bool wide, unsigned grid, size_t lds, hipStream_t st, const ShArgs& a) {
-  if constexpr (BB > 0 && BB <= 8) {
-    if (wide) {
-      hipLaunchKernelGGL((k_sh<BB, FIXT, 4>), dim3(grid), dim3(kShBlock), lds, st, a);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((k_sh<BB, FIXT, 2>), dim3(grid), dim3(kShBlock), lds, st, a);
-}
-}  // namespace
 
 extern "C" int pwfs_sh_forward(pwfs_sh_t s, const float* opd, int nf, float* pixels, float* slopes, void* stream) {
   if (!s) return sfail(PWFS_EINVAL, "plan is NULL");
@@ -445,22 +464,9 @@ extern "C" int pwfs_sh_forward(pwfs_sh_t s, const float* opd, int nf, float* pix
   }
   const unsigned grid = (unsigned)((long long)nf * s->n * s->n);
   hipStream_t st = (hipStream_t)stream;
-  const bool fixt = s->M <= kTFixed;
-  const bool wide = s->r >= 4 * sh_tpp(s->k * s->k, s->r);
-  switch (s->b * 2 + (fixt ? 1 : 0)) {
-    case 9: launch_sh<4, true>(wide, grid, s->lds, st, a); break;
-    case 8: launch_sh<4, false>(wide, grid, s->lds, st, a); break;
-    case 15: launch_sh<7, true>(wide, grid, s->lds, st, a); break;
-    case 14: launch_sh<7, false>(wide, grid, s->lds, st, a); break;
-    case 17: launch_sh<8, true>(wide, grid, s->lds, st, a); break;
-    case 16: launch_sh<8, false>(wide, grid, s->lds, st, a); break;
-    case 33: launch_sh<16, true>(wide, grid, s->lds, st, a); break;
-    case 32: launch_sh<16, false>(wide, grid, s->lds, st, a); break;
-    default:
-      if (fixt) launch_sh<0, true>(wide, grid, s->lds, st, a);
-      else launch_sh<0, false>(wide, grid, s->lds, st, a);
-      break;
-  }
+  sh_pick<1>(sh_half(s->b), s->cols, s->narrow, [&](void (*fn)(ShArgs), int threads) {
+    hipLaunchKernelGGL(fn, dim3(grid), dim3((unsigned)threads), s->lds, st, a);
+  });
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return sfail(PWFS_EHIP, "launch k_sh: %s", hipGetErrorString(e));
   return PWFS_OK;

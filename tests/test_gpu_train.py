@@ -32,8 +32,8 @@ def test_output_bias_gradient_and_loss(n_out, B):
 
 
 @pytest.mark.parametrize("prec", ["BF16", "BF16X3"])
-@pytest.mark.parametrize("M,N,K", [(1, 1024, 32), (63, 1024, 96), (65, 1000, 64), (200, 1023, 192), (4032, 1024, 416), (5, 9, 1),
-                                   (130, 70, 33)])
+@pytest.mark.parametrize("M,N,K", [(1, 1024, 32), (63, 1024, 96), (65, 1000, 64), (200, 1023, 192), (4032, 1024, 416),
+                                   (5, 9, 1), (130, 70, 33)])
 def test_small_tiles_give_the_bits_of_the_large_ones(prec, M, N, K):
     """Rows of a product computed alone (64 x 64 tiles) and inside one of 8192
     rows (the tiles of products that fill the chip): every element adds the same
