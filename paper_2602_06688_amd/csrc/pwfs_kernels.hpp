@@ -752,16 +752,22 @@ __global__ __launch_bounds__(NT) void k_slopes(SlopeArgs p) {
   const float* I = p.in + (long long)f * p.in_stride;
   const int b = BB > 0 ? BB : p.b;
 
+  // four items of a thread at a time have their loads in flight
+#pragma unroll 4
   for (int it = tid; it < 4 * nn; it += NT) {
     const int q = it / nn, s = it % nn;
     const int i = s / p.n, j = s % p.n;
+    // the image's corner by selects: indexed by lane, the arguments would be
+    // loaded from memory first
+    const int org_r = q < 2 ? (q ? p.org_r[1] : p.org_r[0]) : q == 2 ? p.org_r[2] : p.org_r[3];
+    const int org_c = q < 2 ? (q ? p.org_c[1] : p.org_c[0]) : q == 2 ? p.org_c[2] : p.org_c[3];
     float acc = 0.f;
     if constexpr (BB < 0) {
       // subaperture i spans pixels [i img / n, (i + 1) img / n): integer
       // overlaps in units of 1/n pixel, the sum scaled by 1/n^2 at the end
       const int n = p.n, D = p.img;
       const int ylo = i * D, yhi = ylo + D, xlo = j * D, xhi = xlo + D;
-      const float* im = I + (size_t)p.org_r[q] * p.N + p.org_c[q];
+      const float* im = I + (size_t)org_r * p.N + org_c;
       for (int y = ylo / n; y * n < yhi; ++y) {
         const int oy = min((y + 1) * n, yhi) - max(y * n, ylo);
         float row = 0.f;
@@ -773,16 +779,25 @@ __global__ __launch_bounds__(NT) void k_slopes(SlopeArgs p) {
       }
       acc *= 1.0f / (float)(n * n);
     } else if constexpr (BB > 0) {
-      const float* blk = I + (size_t)(p.org_r[q] + i * b) * p.N + p.org_c[q] + j * b;
+      const float* blk = I + (size_t)(org_r + i * b) * p.N + org_c + j * b;
+      // a block's row in loads of up to 16 bytes (4-byte aligned is enough)
+      constexpr int V = BB % 4 == 0 ? 4 : BB;
+      struct __attribute__((packed, aligned(4))) Vec {
+        float v[V];
+      };
       float v[BB * BB];
 #pragma unroll
       for (int r = 0; r < BB; ++r)
 #pragma unroll
-        for (int c = 0; c < BB; ++c) v[r * BB + c] = blk[(size_t)r * p.N + c];
+        for (int c = 0; c < BB; c += V) {
+          const Vec t = *(const Vec*)(blk + (size_t)r * p.N + c);
+#pragma unroll
+          for (int e = 0; e < V; ++e) v[r * BB + c + e] = t.v[e];
+        }
 #pragma unroll
       for (int e = 0; e < BB * BB; ++e) acc += v[e];
     } else {
-      const float* blk = I + (size_t)(p.org_r[q] + i * b) * p.N + p.org_c[q] + j * b;
+      const float* blk = I + (size_t)(org_r + i * b) * p.N + org_c + j * b;
       for (int r = 0; r < b; ++r)
         for (int c = 0; c < b; ++c) acc += blk[(size_t)r * p.N + c];
     }

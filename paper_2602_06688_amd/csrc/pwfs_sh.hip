@@ -3,8 +3,8 @@
 // of 56 x 56 for the SCAO SH).
 //
 // One workgroup per (frame, subaperture), everything in LDS:
-//   E[y][x]  = A exp(i 2 pi OPD / lambda) on the b x b block (float64 phase
-//              reduction, then float32 sincos);
+//   E[y][x]  = A exp(i 2 pi OPD / lambda) on the b x b block (phase formed and
+//              reduced in float64);
 //   T[y][u]  = sum_x E[y][x] W[u][x]          (b x M)
 //   F[v][u]  = sum_y W[v][y] T[y][u]          (M x M, never stored)
 //   pixel P  = sum over its rebin x rebin focal samples of |F|^2, in a fixed
@@ -40,6 +40,7 @@
 
 #include "pwfs.h"
 #include "pwfs_internal.hpp"
+#include "phase_device.hpp"
 
 namespace pwfs {
 namespace {
@@ -66,7 +67,7 @@ struct ShArgs {
   float* slopes;           // [frames][2][n][n]
   int D, n, b, M, r, k, n_lam;
   float wnorm[PWFS_MAX_LAMBDA];             // w_l s_l^2 / (M^2 sum A^2) (monochromatic: 1 / (M^2 sum A^2))
-  double two_pi_over_lam[PWFS_MAX_LAMBDA];
+  double four_over_lam[PWFS_MAX_LAMBDA];
 };
 
 // Folded sizes: h = ceil(b / 2) samples, ceil(M / 2) frequencies.  The rows of
@@ -133,11 +134,8 @@ __global__ __launch_bounds__(NT) void k_sh(ShArgs p) {
     for (int i = tid; i < b * b; i += NT) {
       const int y = i / b, x = i % b;
       const size_t g = (size_t)(si * b + y) * p.D + sj * b + x;
-      const double ph = (double)opd[g] * p.two_pi_over_lam[l];
-      const double nn = rint(ph * 0.15915494309189533577);
-      const float rr = (float)fma(-nn, 6.283185307179586477, ph);
       float sn, cs;
-      sincosf(rr, &sn, &cs);
+      sincos_quarters((double)opd[g] * p.four_over_lam[l], sn, cs);
       const float a = p.amp[g];
       sE[i] = make_float2(a * cs, a * sn);
     }
@@ -301,7 +299,7 @@ struct pwfs_sh_s {
   pwfs_sh_desc d;
   int D, n, b, M, r, k, max_frames, n_valid, n_lam;
   float wnorm[PWFS_MAX_LAMBDA];
-  double two_pi_over_lam[PWFS_MAX_LAMBDA];
+  double four_over_lam[PWFS_MAX_LAMBDA];
   float* amp = nullptr;
   float2* W = nullptr;
   uint8_t* valid = nullptr;
@@ -412,7 +410,7 @@ extern "C" int pwfs_sh_plan(const pwfs_sh_desc* d, int max_frames, void* ws, siz
   s->n_lam = nl;
   for (int l = 0; l < nl; ++l) {
     s->wnorm[l] = (float)(wgt[l] * scale[l] * scale[l] / ((double)M * M * sA2));
-    s->two_pi_over_lam[l] = 2.0 * kPiSh / lam[l];
+    s->four_over_lam[l] = 4.0 / lam[l];
   }
   char* p = (char*)ws;
   s->amp = (float*)p;
@@ -460,7 +458,7 @@ extern "C" int pwfs_sh_forward(pwfs_sh_t s, const float* opd, int nf, float* pix
   a.n_lam = s->n_lam;
   for (int l = 0; l < s->n_lam; ++l) {
     a.wnorm[l] = s->wnorm[l];
-    a.two_pi_over_lam[l] = s->two_pi_over_lam[l];
+    a.four_over_lam[l] = s->four_over_lam[l];
   }
   const unsigned grid = (unsigned)((long long)nf * s->n * s->n);
   hipStream_t st = (hipStream_t)stream;

@@ -59,6 +59,8 @@
 
 #include "fft_device.hpp"
 #include "mfma_gemm.hpp"
+#include "phase_device.hpp"
+#include "pwfs.h"
 
 namespace pwfs {
 
@@ -95,8 +97,45 @@ constexpr int kToepZExp = 10, kToepKExp = 10;
 // padding.
 __host__ __device__ constexpr int toep_block_floats(int Dq) { return Dq / 8 * 512; }
 
+// real part of sample j' of parity q of a line (the imaginary part is 4 floats on)
+__device__ __forceinline__ size_t toep_at(int Dq, int line, int jq, int q) {
+  return (size_t)(line >> 4) * toep_block_floats(Dq) +
+         (((jq >> 3) * 2 + q) * 2 + ((jq >> 2) & 1)) * 128 + 8 * (line & 15) + (jq & 3);
+}
+
+struct ToepFieldArgs {
+  const float* opd;        // [frames][opd_stride]
+  const float* amp;        // [D][D]
+  long long opd_stride;
+  int D, Dh, Dq;
+  double four_over_lam[PWFS_MAX_LAMBDA];
+};
+
+// Samples 2 x' and 2 x' + 1 of a line of a frame's rows: A exp(i 2 pi OPD /
+// lambda), the phase formed and reduced in float64; out points at the line's block.  A sample that is not finite makes its whole
+// 2 x 2 block of pixels NaN, so both parities of its row and column carry it and
+// every output of the frame becomes NaN, as it does through a full transform.
+// The padding is zeroed: the passes read it against zero factors.
+__device__ __forceinline__ void toep_field2(const ToepFieldArgs& p, int f, int lam, int line, int xh, float* out) {
+  const int yp = line >= p.Dq ? 1 : 0, yh = line - yp * p.Dq;
+  const bool in = yh < p.Dh && xh < p.Dh;
+  const float* o = p.opd + (long long)f * p.opd_stride;
+  const int at = in ? (2 * yh + yp) * p.D + 2 * xh : 0, other = in ? at + (yp ? -p.D : p.D) : 0;
+  const float o0 = o[at], o1 = o[at + 1];
+  const float bad = in ? 0.f * o0 + 0.f * o1 + 0.f * o[other] + 0.f * o[other + 1] : 0.f;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    float sn, cs;
+    sincos_quarters(in ? (double)(q ? o1 : o0) * p.four_over_lam[lam] : 0.0, sn, cs);
+    const float a = in ? p.amp[at + q] : 0.f;
+    float* l = out + toep_at(p.Dq, line & 15, xh, q);
+    l[0] = a * cs + bad;
+    l[4] = a * sn + bad;
+  }
+}
+
 struct ToepRowArgs {
-  const float* field;      // [frames][n_lam][Dq / 8] blocks of rows
+  ToepFieldArgs field;
   float* rbuf;             // [frames][n_lam][cblocks][n_a] blocks of columns, 2^20 x the row output
   const uint16_t* atab;    // [2][toep_table_len]
   const float* rtab;       // [n_lam][n_a][2][toep_r_len]
@@ -301,19 +340,13 @@ __device__ __forceinline__ void toep_stage(uint16_t* s_tab, const uint16_t* tab,
   for (int i = tid; i < n16; i += nt) ((u32x4_t*)s_tab)[i] = ((const u32x4_t*)tab)[i];
 }
 
-// Direct loads of a block into LDS, 1 KB per instruction, chunks wave, wave +
-// waves, ... of its Dq / 4.  The wave waits for its own (toep_landed) before the
-// barrier after which the others read them.
-__device__ __forceinline__ void toep_bring(float* s_x, const float* blk, int Dq, int wave, int waves, int lane) {
-  for (int k = wave; k < Dq / 4; k += waves)
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(blk + k * 256 + 4 * lane),
-                                     (__attribute__((address_space(3))) void*)(s_x + k * 256), 16, 0, 0);
-}
+// the wavefront's memory operations have been carried out
 __device__ __forceinline__ void toep_landed() { __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---------------------------------------------------------------- rows ----
-// 4 wavefronts share a row block: 2 parities x alternate keys.  The block stays
-// in LDS for all keys.  Each tile is turned around in LDS (a lane holds one line
+// 4 wavefronts share a row block: 2 parities x alternate keys.  They form the
+// block's field in LDS, where it stays for all keys (a pass of its own wrote and
+// read it: 31 us per 200 frames of 160 px, and a launch).  Each tile is turned around in LDS (a lane holds one line
 // and 16 output samples; a column block wants 4 consecutive lines of one sample)
 // and leaves in 16-byte stores, four runs of 256 contiguous bytes per
 // instruction.
@@ -337,9 +370,11 @@ __device__ __forceinline__ void toep_rows_body(const ToepRowArgs& p, int bid, un
   const int agi = bid % p.n_agroups, lam = bid / p.n_agroups;
   const int rblocks = p.Dq / 8, bf = toep_block_floats(p.Dq);
   const int f = lg / rblocks, rb = lg - f * rblocks;
-  toep_bring(s_x, p.field + (((size_t)f * p.n_lam + lam) * rblocks + rb) * bf, p.Dq, wave, 4, lane);
   toep_stage<KS>(s_tab, p.atab, tid, kToepRowThreads);
-  toep_landed();
+  // the field of the block's lines, 16 lanes side by side along a line
+#pragma unroll
+  for (int i = 0; i < KS; ++i)
+    if ((tid & 15) + 16 * i < p.Dq) toep_field2(p.field, f, lam, rb * kToepLines + (tid >> 4), (tid & 15) + 16 * i, s_x);
   __syncthreads();
   float* s_turn = s_x + 1024 * KS + wave * kToepTurn;
   const int a0 = agi * p.ag + (wave >> 1), a1 = min((agi + 1) * p.ag, p.n_a);

@@ -16,11 +16,12 @@
 #include "pwfs.h"
 #include "pwfs_geom.hpp"
 #include "pwfs_internal.hpp"
-#include "toep_field.hpp"
+#include "toep_persistent.hpp"
 
 namespace pwfs {
 namespace {
 
+constexpr int kToepBlock = 256;
 constexpr double kPiT = 3.14159265358979323846264338327950288;
 size_t ta256(size_t x) { return (x + 255) & ~size_t(255); }
 
@@ -119,8 +120,14 @@ void toep_limits() {
   toep_limit1<8>();
 }
 
-__global__ __launch_bounds__(kToepBlock) void k_toep_field(ToepFieldArgs p) {
-  toep_field_body(p, blockIdx.x, threadIdx.x);
+// the field in row blocks ([frames][n_lam][Dq / 8]) for arm y of a double roof
+__global__ __launch_bounds__(kToepBlock) void k_toep_field(ToepFieldArgs p, float* field, int n_lam) {
+  const int per = 2 * p.Dq * p.Dq, blocks = (per + kToepBlock - 1) / kToepBlock;
+  const int fl = blockIdx.x / blocks, i = (blockIdx.x - fl * blocks) * kToepBlock + threadIdx.x;
+  if (i >= per) return;
+  const int line = i / p.Dq;
+  toep_field2(p, fl / n_lam, fl % n_lam, line, i - line * p.Dq,
+              field + ((size_t)fl * (p.Dq / 8) + (line >> 4)) * toep_block_floats(p.Dq));
 }
 
 // The flat axis of a double-roof arm without a field stop is the identity (up
@@ -220,12 +227,12 @@ size_t toep_table_bytes(const pwfs_sensor_desc& d) {
          ta256(sizeof(float) * 2 * toep_r_len(t.KS) * (size_t)g.n_lam * g.n_mod);
 }
 
-// per frame: the row output, then the field (the field block of a pass sits
-// after all frames' row output)
+// per frame: the row output, then, for the flat axis of a double roof, the field
+// (the field block of a pass sits after all frames' row output)
 size_t toep_scratch_frame_bytes(const pwfs_sensor_desc& d) {
   const ToepGeom t = toep_geom(d);
   const Geometry g = geometry(d);
-  return sizeof(float) * toep_block_floats(t.Dq) * (size_t)g.n_lam * ((size_t)g.n_a * toep_cblocks(g, t) + t.Dq / 8);
+  return sizeof(float) * toep_block_floats(t.Dq) * (size_t)g.n_lam * ((size_t)g.n_a * toep_cblocks(g, t) + (sensor_arms(d) == 2 ? t.Dq / 8 : 0));
 }
 
 // Unit sums of the split column pass, kept behind a pass's frames.  At most 256
@@ -370,10 +377,9 @@ namespace {
 
 // Arguments of the three passes of one sensor over nf frames.
 struct ToepPass {
-  ToepFieldArgs fa;
   ToepRowArgs ra;
   ToepColArgs ca;
-  unsigned grid_field, grid_rows, grid_cols;
+  unsigned grid_rows, grid_cols;
 };
 
 ToepPass toep_pass(const SensorPlan& sp, const ToepGeom& t, const float* opd, long long opd_stride, float* out,
@@ -382,7 +388,6 @@ ToepPass toep_pass(const SensorPlan& sp, const ToepGeom& t, const float* opd, lo
   ToepPass tp{};
   float* R = (float*)rbuf;
   const int cblocks = toep_cblocks(g, t);
-  float* field = R + (size_t)nf * g.n_lam * g.n_a * cblocks * toep_block_floats(t.Dq);
   const char* tb = (const char*)sp.dev[R_TOEP];
   const uint16_t* atab = (const uint16_t*)tb;
   tb += ta256(sizeof(uint16_t) * 2 * toep_table_len(t.KS));
@@ -390,20 +395,15 @@ ToepPass toep_pass(const SensorPlan& sp, const ToepGeom& t, const float* opd, lo
   tb += ta256(sizeof(float) * 2 * toep_r_len(t.KS) * (size_t)g.n_lam * g.n_a);
   const float* ry = (const float*)tb;
 
-  ToepFieldArgs& fa = tp.fa;
+  ToepRowArgs& ra = tp.ra;
+  ToepFieldArgs& fa = ra.field;
   fa.opd = opd;
   fa.amp = (const float*)sp.dev[R_AMP];
-  fa.field = field;
   fa.opd_stride = opd_stride;
   fa.D = g.D;
   fa.Dh = t.Dh;
   fa.Dq = t.Dq;
-  fa.n_lam = g.n_lam;
-  for (int l = 0; l < g.n_lam; ++l) fa.two_pi_over_lam[l] = 2.0 * kPiT / sp.desc.lambda_nm[l];
-  tp.grid_field = (unsigned)(nf * g.n_lam * ((t.Dq * t.Dq + kToepBlock - 1) / kToepBlock));
-
-  ToepRowArgs& ra = tp.ra;
-  ra.field = field;
+  for (int l = 0; l < g.n_lam; ++l) fa.four_over_lam[l] = 4.0 / sp.desc.lambda_nm[l];
   ra.rbuf = R;
   ra.atab = atab;
   ra.rtab = rx;
@@ -479,14 +479,20 @@ int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, f
   const ToepGeom t = toep_geom(sp.desc);
   ToepPass tp = toep_pass(sp, t, opd, opd_stride, out, out_stride, nf, rbuf, 512);
   hipError_t e;
-  int slot = prof->begin(st);
-  hipLaunchKernelGGL(k_toep_field, dim3(tp.grid_field), dim3(kToepBlock), 0, st, tp.fa);
-  if ((e = hipGetLastError()) != hipSuccess) return toep_failed(e, "k_toep_field");
-  prof->end(slot, st, K_FIELD);
+  int slot;
+  // behind the pass's row output (the sums of a split pass lie behind it)
+  float* field = (float*)rbuf + (size_t)nf * g.n_lam * g.n_a * tp.ca.cblocks * toep_block_floats(t.Dq);
+  if (sp.ident == 2) {
+    slot = prof->begin(st);
+    const unsigned grid = (unsigned)(nf * g.n_lam * ((2 * t.Dq * t.Dq + kToepBlock - 1) / kToepBlock));
+    hipLaunchKernelGGL(k_toep_field, dim3(grid), dim3(kToepBlock), 0, st, tp.ra.field, field, g.n_lam);
+    if ((e = hipGetLastError()) != hipSuccess) return toep_failed(e, "k_toep_field");
+    prof->end(slot, st, K_FIELD);
+  }
 
   ToepIdentArgs ia{};
   if (sp.ident) {
-    ia.field = tp.ra.field;
+    ia.field = field;
     ia.rx = (const float2*)sp.dev[R_RX];
     ia.rbuf = tp.ra.rbuf;
     ia.kord = tp.ca.kord;
@@ -551,16 +557,14 @@ int forward_toep_hetero(pwfs_plan_s* p, const std::vector<int>& which, const flo
     const ToepPass tp = toep_pass(sp, t, opd + sp.opd_offset + (long long)f0 * p->opd_stride,
                                   (long long)p->opd_stride, out + sp.int_offset + (long long)f0 * p->int_stride,
                                   (long long)p->int_stride, nf, sp.rbuf, p->tune.row_groups);
-    ha.field[i] = tp.fa;
     ha.rows[i] = tp.ra;
     ha.cols[i] = tp.ca;
     ha.ks[i] = t.KS;
-    ha.n_items[0][i] = (int)tp.grid_field;
-    ha.n_items[1][i] = (int)tp.grid_rows;
-    ha.n_items[2][i] = (int)tp.grid_cols;
+    ha.n_items[0][i] = (int)tp.grid_rows;
+    ha.n_items[1][i] = (int)tp.grid_cols;
     lds = std::max(lds, toep_lds_of(t.KS));
     cost.push_back({-(double)sp.g.n_mod * sp.g.n_lam * sp.g.D * sp.g.D, (int)i});
-    for (int k = 0; k < 3; ++k) ha.total += ha.n_items[k][i];
+    for (int k = 0; k < 2; ++k) ha.total += ha.n_items[k][i];
   }
   std::sort(cost.begin(), cost.end());
   for (size_t i = 0; i < cost.size(); ++i) ha.order[i] = cost[i].second;   // largest sensors claim first

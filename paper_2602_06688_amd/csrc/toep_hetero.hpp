@@ -6,7 +6,7 @@
 // of one wave per SIMD.
 #pragma once
 
-#include "toep_field.hpp"
+#include "toep_persistent.hpp"
 
 namespace pwfs {
 
@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256, 1) void k_toep_hetero(ToepHeteroArgs) {
     __syncthreads();
     if (item >= p.total) break;
     int kind = 0, s = 0;
-    for (kind = 0; kind < 3; ++kind) {
+    for (kind = 0; kind < 2; ++kind) {
       bool found = false;
       for (int o = 0; o < p.n_sensors; ++o) {
         const int c = p.n_items[kind][p.order[o]];
@@ -45,8 +45,8 @@ __global__ __launch_bounds__(256, 1) void k_toep_hetero(ToepHeteroArgs) {
     bool skip = false;
     if (kind > 0) {
       if (threadIdx.x == 0) {
-        int* dep = &p.counters[1 + 2 * s + (kind - 1)];
-        const int need = p.n_items[kind - 1][s];
+        int* dep = &p.counters[1 + s];
+        const int need = p.n_items[0][s];
         int spins = 0, gave_up = p.spin_limit < 0;
         while (!gave_up && __hip_atomic_load(dep, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < need) {
           __builtin_amdgcn_s_sleep(2);
@@ -61,8 +61,6 @@ __global__ __launch_bounds__(256, 1) void k_toep_hetero(ToepHeteroArgs) {
     if (skip) {
       // the item's inputs may be incomplete: leave its outputs untouched
     } else if (kind == 0) {
-      toep_field_body(p.field[s], item, tid);
-    } else if (kind == 1) {
       switch (p.ks[s]) {
         case 1: toep_rows_body<1>(p.rows[s], item, toep_smem, tid); break;
         case 2: toep_rows_body<2>(p.rows[s], item, toep_smem, tid); break;
@@ -87,8 +85,8 @@ __global__ __launch_bounds__(256, 1) void k_toep_hetero(ToepHeteroArgs) {
     }
     toep_landed();     // this wavefront's stores have reached the L2 ...
     __syncthreads();   // ... and every other's; the LDS is free
-    if (threadIdx.x == 0 && kind < 2)
-      __hip_atomic_fetch_add(&p.counters[1 + 2 * s + kind], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    if (threadIdx.x == 0 && kind == 0)
+      __hip_atomic_fetch_add(&p.counters[1 + s], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
