@@ -44,7 +44,8 @@ int mfail(int code, const char* fmt, ...) {
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 int up32(int x) { return (x + 31) / 32 * 32; }
 
-enum Epi { E_STORE = 0, E_HIDDEN = 1, E_OUTPUT = 2, E_DHIDDEN = 3 };
+// E_PREDICT: the output layer without a target
+enum Epi { E_STORE = 0, E_HIDDEN = 1, E_OUTPUT = 2, E_DHIDDEN = 3, E_PREDICT = 4 };
 
 struct GemmArgs {
   const uint16_t* a;
@@ -107,46 +108,95 @@ __device__ __forceinline__ void put16x4(uint16_t* base, long long plane, long lo
     *(uint2*)(base + plane + off) = make_uint2(lo[0] | (uint32_t)lo[1] << 16, lo[2] | (uint32_t)lo[3] << 16);
 }
 
-// the epilogue of the outputs (m .. m + 3, n) of a product whose accumulated
-// values are v (m a multiple of 4; rows from p.M on are not written); lsum
-// collects the squared error (E_OUTPUT with a target).  Transposed copies exist
-// in training only, whose M (the batch) and ldht are multiples of 32: they leave
-// in 8-byte stores.
+// What the epilogue of a 32 x 32 tile reads, loaded before its first store: a
+// load behind a store waits until the store is done (both count in order), so
+// reading the bias beside each store cost a round trip per element (output layer
+// of 20000 x 3200: 346 us, the same product without a bias 260 us).
 template <int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, int m, int n, const float (&v)[4], double& lsum) {
-  float t[4] = {0.f, 0.f, 0.f, 0.f};
+struct TileAux {
+  float bias = 0.f, v[16];
+  // row(e): row of accumulator element e
+  template <class Row>
+  __device__ __forceinline__ void load(const GemmArgs& p, int n, Row row) {
+    if constexpr (EPI == E_HIDDEN || EPI == E_OUTPUT || EPI == E_PREDICT) bias = p.bias[n];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    if (m + r >= p.M) break;
-    const long long mr = m + r;
-    if constexpr (EPI == E_STORE) {
-      float* cp = p.c + mr * p.ldc + n;
-      *cp = (p.beta != 0.f) ? p.alpha * v[r] + p.beta * *cp : p.alpha * v[r];
-    } else if constexpr (EPI == E_HIDDEN) {
-      const float zz = v[r] + p.bias[n];
-      t[r] = gelu_f(zz);
-      put16(p.h, p.h_plane, mr * p.ldh + n, t[r], p.planes_out);
-      // the pre-activation and the transposed copy serve the backward
-      // pass only (absent in inference)
-      if (p.z) p.z[mr * p.ldz + n] = zz;
-    } else if constexpr (EPI == E_OUTPUT) {
-      const float y = v[r] + p.bias[n];
-      if (p.c) p.c[mr * p.ldc + n] = p.alpha * y;
-      if (p.target) {
-        const float d = y - p.target[mr * p.ldt + n] * p.tscale;
-        lsum += (double)d * d;
-        t[r] = p.gscale * d;
+    for (int e = 0; e < 16; ++e) {
+      const long long m = min(row(e), p.M - 1);
+      v[e] = 0.f;
+      if constexpr (EPI == E_STORE) {
+        if (p.beta != 0.f) v[e] = p.c[m * p.ldc + n];
+      } else if constexpr (EPI == E_OUTPUT) {
+        if (p.target) v[e] = p.target[m * p.ldt + n];
+      } else if constexpr (EPI == E_DHIDDEN) {
+        v[e] = p.zprev[m * p.ldzp + n];
+      }
+    }
+  }
+};
+
+// the epilogue of a 32 x 32 tile (column n of this lane; row(e) is the row of
+// accumulator element e, of four elements consecutive; rows from p.M on are not
+// written) whose accumulated values are val(e); lsum collects the squared error
+// (E_OUTPUT with a target).  Transposed copies exist in training only, whose M
+// (the batch) and ldht are multiples of 32: they leave in 8-byte stores.
+template <int EPI, class Row, class Val>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, int n, Row row, Val val, double& lsum) {
+  if (n >= p.N) return;
+  TileAux<EPI> aux;
+  aux.load(p, n, row);
+#pragma unroll
+  for (int e0 = 0; e0 < 16; e0 += 4) {
+    float t[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = row(e0 + r);
+      if (m >= p.M) break;
+      const long long mr = m;
+      const float v = val(e0 + r);
+      if constexpr (EPI == E_STORE) {
+        p.c[mr * p.ldc + n] = (p.beta != 0.f) ? p.alpha * v + p.beta * aux.v[e0 + r] : p.alpha * v;
+      } else if constexpr (EPI == E_HIDDEN) {
+        const float zz = v + aux.bias;
+        t[r] = gelu_f(zz);
+        put16(p.h, p.h_plane, mr * p.ldh + n, t[r], p.planes_out);
+        // the pre-activation and the transposed copy serve the backward
+        // pass only (absent in inference)
+        if (p.z) p.z[mr * p.ldz + n] = zz;
+      } else if constexpr (EPI == E_PREDICT) {
+        p.c[mr * p.ldc + n] = p.alpha * (v + aux.bias);
+      } else if constexpr (EPI == E_OUTPUT) {
+        const float y = v + aux.bias;
+        if (p.c) p.c[mr * p.ldc + n] = p.alpha * y;
+        if (p.target) {
+          const float d = y - aux.v[e0 + r] * p.tscale;
+          lsum += (double)d * d;
+          t[r] = p.gscale * d;
+          p.z[mr * p.ldz + n] = t[r];
+          put16(p.h, p.h_plane, mr * p.ldh + n, t[r], p.planes_out);
+        }
+      } else {  // E_DHIDDEN
+        t[r] = v * gelu_grad_f(aux.v[e0 + r]);
         p.z[mr * p.ldz + n] = t[r];
         put16(p.h, p.h_plane, mr * p.ldh + n, t[r], p.planes_out);
       }
-    } else {  // E_DHIDDEN
-      t[r] = v[r] * gelu_grad_f(p.zprev[mr * p.ldzp + n]);
-      p.z[mr * p.ldz + n] = t[r];
-      put16(p.h, p.h_plane, mr * p.ldh + n, t[r], p.planes_out);
     }
+    const int m = row(e0);
+    if constexpr (EPI != E_STORE && EPI != E_PREDICT)
+      if (p.ht && m < p.M) put16x4(p.ht, p.ht_plane, (long long)n * p.ldht + m, t, p.planes_out);
   }
-  if constexpr (EPI != E_STORE)
-    if (p.ht && m < p.M) put16x4(p.ht, p.ht_plane, (long long)n * p.ldht + m, t, p.planes_out);
+}
+
+// Tile of a workgroup.  Workgroups are dealt to the 8 XCDs in turn: each XCD gets
+// a contiguous eighth of the tiles, in columns of kTileRows row tiles, so that
+// the tiles it runs together share their operand rows in its L2.
+constexpr int kTileRows = 4;
+__device__ __forceinline__ void tile_of(int b, int mtiles, int ntiles, int& mt, int& nt) {
+  const int total = mtiles * ntiles, q = total >> 3, r = total & 7, x = b & 7;
+  const int i = x * q + min(x, r) + (b >> 3);
+  const int band = i / (kTileRows * ntiles), in = i - band * kTileRows * ntiles;
+  const int rows = min(kTileRows, mtiles - band * kTileRows);
+  nt = in / rows;
+  mt = band * kTileRows + in - nt * rows;
 }
 
 // the squared error of a workgroup of 256 lanes
@@ -168,8 +218,8 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs p) {
   uint16_t* lds = (uint16_t*)lds_raw;
   using E = MfmaTile<NPL, false, BK>;
   const int tid = threadIdx.x;
-  const int nt = blockIdx.x % p.ntiles;
-  const int mt = blockIdx.x / p.ntiles;
+  int mt, nt;
+  tile_of(blockIdx.x, p.mtiles, p.ntiles, mt, nt);
   const int m0 = mt * kGemmTile, n0 = nt * kGemmTile;
   typename E::Ops ops;
 #pragma unroll
@@ -194,15 +244,12 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs p) {
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; e += 4) {
-        int row, col;
-        E::coord(tid, i, j, e, row, col);
-        const int m = m0 + row, n = n0 + col;
-        if (m >= p.M || n >= p.N) continue;
-        const float v[4] = {eng.value(i, j, e), eng.value(i, j, e + 1), eng.value(i, j, e + 2), eng.value(i, j, e + 3)};
-        gemm_epilogue<EPI>(p, m, n, v, lsum);
-      }
+    {
+      int row0, col;
+      E::coord(tid, i, j, 0, row0, col);
+      gemm_epilogue<EPI>(p, n0 + col, [&](int e) { return m0 + row0 + 8 * (e >> 2) + (e & 3); },
+                         [&](int e) { return eng.value(i, j, e); }, lsum);
+    }
   if constexpr (EPI == E_OUTPUT) loss_partial(p, lsum, tid);
 }
 
@@ -221,7 +268,8 @@ __global__ __launch_bounds__(256) void k_gemm_small(GemmArgs p) {
   constexpr int DEPTH = 3, CPR = BK / 8, RPP = 256 / CPR, CH = NPL * 2 * kSmallTile / RPP, LROW = BK + 8;
   __shared__ __align__(16) uint16_t lds[2][gemm_small_stage<NPL, BK>()];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
-  const int nt = blockIdx.x % p.ntiles, mt = blockIdx.x / p.ntiles;
+  int mt, nt;
+  tile_of(blockIdx.x, p.mtiles, p.ntiles, mt, nt);
   const int m0 = mt * kSmallTile, n0 = nt * kSmallTile;
   const int nk1 = p.K / BK, steps = nk1 + p.K2 / BK;
   const int kq = (tid % CPR) * 8;
@@ -282,14 +330,9 @@ __global__ __launch_bounds__(256) void k_gemm_small(GemmArgs p) {
     }
   }
   double lsum = 0.0;
-  const int n = n0 + wn * 32 + (lane & 31);
-  if (n < p.N)
-#pragma unroll
-    for (int e = 0; e < 16; e += 4) {
-      const int m = m0 + wm * 32 + 8 * (e >> 2) + 4 * (lane >> 5);
-      const float v[4] = {acc[e], acc[e + 1], acc[e + 2], acc[e + 3]};
-      if (m < p.M) gemm_epilogue<EPI>(p, m, n, v, lsum);
-    }
+  gemm_epilogue<EPI>(p, n0 + wn * 32 + (lane & 31),
+                     [&](int e) { return m0 + wm * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); },
+                     [&](int e) { return acc[e]; }, lsum);
   if constexpr (EPI == E_OUTPUT) loss_partial(p, lsum, tid);
 }
 
@@ -310,8 +353,8 @@ __global__ __launch_bounds__(64 * (2 * BN / 64 + 4)) void k_gemm_ws(GemmArgs p) 
   constexpr int NC = 2 * BN / 64, BK = E::BK_, CH = W::CH;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nt = blockIdx.x % p.ntiles;
-  const int mt = blockIdx.x / p.ntiles;
+  int mt, nt;
+  tile_of(blockIdx.x, p.mtiles, p.ntiles, mt, nt);
   const int m0 = mt * kGemmTile, n0 = nt * BN;
   const int nk1 = p.K / BK;
   const int steps = nk1 + p.K2 / BK;
@@ -361,15 +404,10 @@ __global__ __launch_bounds__(64 * (2 * BN / 64 + 4)) void k_gemm_ws(GemmArgs p) 
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; e += 4) {
-        // accumulator layout of the 32 x 32 tile (i, j) of this quarter
-        const int m = m0 + wm * 64 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5);
-        const int n = n0 + wn * 64 + j * 32 + (lane & 31);
-        if (m >= p.M || n >= p.N) continue;
-        const float v[4] = {eng.value(i, j, e), eng.value(i, j, e + 1), eng.value(i, j, e + 2), eng.value(i, j, e + 3)};
-        gemm_epilogue<EPI>(p, m, n, v, lsum);
-      }
+      // accumulator layout of the 32 x 32 tile (i, j) of this quarter
+      gemm_epilogue<EPI>(p, n0 + wn * 64 + j * 32 + (lane & 31),
+                         [&](int e) { return m0 + wm * 64 + i * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3); },
+                         [&](int e) { return eng.value(i, j, e); }, lsum);
 }
 
 // fp32 [rows][cols] (row stride ld) -> 16-bit planes [rows][ldo], zero padding up
@@ -619,6 +657,8 @@ bool small_tiles(int planes, int M, int N) {
 
 template <int EPI>
 int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
+  if constexpr (EPI == E_OUTPUT)
+    if (!a.target) return gemm_dispatch<E_PREDICT>(planes, a, st);
   if (small_tiles(planes, a.M, a.N)) {
     if (planes == 2) return gemm_small_launch<2, EPI, 32>(a, st);
     if (a.K % 64 != 0 || a.K2 % 64 != 0) return gemm_small_launch<1, EPI, 32>(a, st);
@@ -626,12 +666,10 @@ int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
   }
   if (planes == 2) return gemm_launch<2, EPI, 32>(a, st);
   if (a.K % 64 != 0 || a.K2 % 64 != 0) return gemm_launch<1, EPI, 32>(a, st);
-  if constexpr (EPI != E_DHIDDEN) {
-    if (EPI != E_OUTPUT || !a.target) {
-      const long long mt = (a.M + kGemmTile - 1) / kGemmTile;
-      if (mt * ((a.N + 255) / 256) >= kWsWideTiles) return gemm_ws_launch<EPI, 256>(a, st);
-      if (mt * ((a.N + 127) / 128) >= kWsMinTiles) return gemm_ws_launch<EPI, 128>(a, st);
-    }
+  if constexpr (EPI != E_DHIDDEN && EPI != E_OUTPUT) {
+    const long long mt = (a.M + kGemmTile - 1) / kGemmTile;
+    if (mt * ((a.N + 255) / 256) >= kWsWideTiles) return gemm_ws_launch<EPI, 256>(a, st);
+    if (mt * ((a.N + 127) / 128) >= kWsMinTiles) return gemm_ws_launch<EPI, 128>(a, st);
   }
   return gemm_launch<1, EPI, 64>(a, st);
 }
