@@ -642,8 +642,11 @@ int gemm_ws_launch(const GemmArgs& a0, hipStream_t st) {
 // One-plane products with at least two rounds of wave-specialised
 // workgroups on the chip (one per CU) and no loss epilogue take the
 // wave-specialised tiles: 128 x 256 where that still gives four rounds,
-// else 128 x 128.  The rest (training batches, two-plane checks, the loss
-// and gradient epilogues) take the 256-lane tiles.
+// else 128 x 128.  The rest (two-plane products, the loss and gradient
+// epilogues) take the 256-lane tiles, and so do hidden layers on 128 x 128
+// tiles: two workgroups share a CU there, and the GELU of one (43 us of vector
+// issue for 20000 x 1024) runs beside the products of the other (a prediction of
+// 20000 samples: 440 us, 451 us wave-specialised).
 constexpr int kWsMinTiles = 512, kWsWideTiles = 1024;
 
 // Products of fewer 128 x 128 tiles than two rounds of the chip take 64 x 64
@@ -669,7 +672,7 @@ int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
   if constexpr (EPI != E_DHIDDEN && EPI != E_OUTPUT) {
     const long long mt = (a.M + kGemmTile - 1) / kGemmTile;
     if (mt * ((a.N + 255) / 256) >= kWsWideTiles) return gemm_ws_launch<EPI, 256>(a, st);
-    if (mt * ((a.N + 127) / 128) >= kWsMinTiles) return gemm_ws_launch<EPI, 128>(a, st);
+    if (EPI != E_HIDDEN && mt * ((a.N + 127) / 128) >= kWsMinTiles) return gemm_ws_launch<EPI, 128>(a, st);
   }
   return gemm_launch<1, EPI, 64>(a, st);
 }
