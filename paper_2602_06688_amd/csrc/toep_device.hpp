@@ -116,21 +116,33 @@ struct ToepFieldArgs {
 // 2 x 2 block of pixels NaN, so both parities of its row and column carry it and
 // every output of the frame becomes NaN, as it does through a full transform.
 // The padding is zeroed: the passes read it against zero factors.
-__device__ __forceinline__ void toep_field2(const ToepFieldArgs& p, int f, int lam, int line, int xh, float* out) {
+struct ToepPixels {
+  float opd[2], amp[2], bad;
+};
+__device__ __forceinline__ ToepPixels toep_pixels(const ToepFieldArgs& p, int f, int line, int xh) {
   const int yp = line >= p.Dq ? 1 : 0, yh = line - yp * p.Dq;
   const bool in = yh < p.Dh && xh < p.Dh;
   const float* o = p.opd + (long long)f * p.opd_stride;
   const int at = in ? (2 * yh + yp) * p.D + 2 * xh : 0, other = in ? at + (yp ? -p.D : p.D) : 0;
-  const float o0 = o[at], o1 = o[at + 1];
-  const float bad = in ? 0.f * o0 + 0.f * o1 + 0.f * o[other] + 0.f * o[other + 1] : 0.f;
+  ToepPixels v;
+  v.opd[0] = o[at];
+  v.opd[1] = o[at + 1];
+  v.bad = 0.f * o[other] + 0.f * o[other + 1];
+  v.amp[0] = p.amp[at];
+  v.amp[1] = p.amp[at + 1];
+  if (!in) v = ToepPixels{};
+  return v;
+}
+__device__ __forceinline__ void toep_field2(const ToepFieldArgs& p, const ToepPixels& v, int lam, int line, int xh,
+                                            float* out) {
+  const float bad = 0.f * v.opd[0] + 0.f * v.opd[1] + v.bad;
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     float sn, cs;
-    sincos_quarters(in ? (double)(q ? o1 : o0) * p.four_over_lam[lam] : 0.0, sn, cs);
-    const float a = in ? p.amp[at + q] : 0.f;
+    sincos_quarters((double)v.opd[q] * p.four_over_lam[lam], sn, cs);
     float* l = out + toep_at(p.Dq, line & 15, xh, q);
-    l[0] = a * cs + bad;
-    l[4] = a * sn + bad;
+    l[0] = v.amp[q] * cs + bad;
+    l[4] = v.amp[q] * sn + bad;
   }
 }
 
@@ -370,11 +382,16 @@ __device__ __forceinline__ void toep_rows_body(const ToepRowArgs& p, int bid, un
   const int agi = bid % p.n_agroups, lam = bid / p.n_agroups;
   const int rblocks = p.Dq / 8, bf = toep_block_floats(p.Dq);
   const int f = lg / rblocks, rb = lg - f * rblocks;
+  // the field of the block's lines, 16 lanes side by side along a line; its loads
+  // travel while the tables are staged
+  ToepPixels px[KS];
+#pragma unroll
+  for (int i = 0; i < KS; ++i) px[i] = toep_pixels(p.field, f, rb * kToepLines + (tid >> 4), (tid & 15) + 16 * i);
   toep_stage<KS>(s_tab, p.atab, tid, kToepRowThreads);
-  // the field of the block's lines, 16 lanes side by side along a line
 #pragma unroll
   for (int i = 0; i < KS; ++i)
-    if ((tid & 15) + 16 * i < p.Dq) toep_field2(p.field, f, lam, rb * kToepLines + (tid >> 4), (tid & 15) + 16 * i, s_x);
+    if ((tid & 15) + 16 * i < p.Dq)
+      toep_field2(p.field, px[i], lam, rb * kToepLines + (tid >> 4), (tid & 15) + 16 * i, s_x);
   __syncthreads();
   float* s_turn = s_x + 1024 * KS + wave * kToepTurn;
   const int a0 = agi * p.ag + (wave >> 1), a1 = min((agi + 1) * p.ag, p.n_a);
@@ -562,6 +579,7 @@ __device__ __forceinline__ void toep_sum_body(const ToepColArgs& p, int bid, int
   const size_t stride = (size_t)p.lgroups * 2 * 8 * KS * 64;
   const float* v = p.part + (size_t)i * 64 + lane;
   float acc = v[0];
+#pragma unroll 8
   for (int u = 1; u < p.units; ++u) acc += v[u * stride];
   const int n = lane & 31, h = lane >> 5, f = lg / p.cblocks;
   int X, Y;

@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kToepBlock) void k_toep_field(ToepFieldArgs p, floa
   const int fl = blockIdx.x / blocks, i = (blockIdx.x - fl * blocks) * kToepBlock + threadIdx.x;
   if (i >= per) return;
   const int line = i / p.Dq;
-  toep_field2(p, fl / n_lam, fl % n_lam, line, i - line * p.Dq,
+  toep_field2(p, toep_pixels(p, fl / n_lam, line, i - line * p.Dq), fl % n_lam, line, i - line * p.Dq,
               field + ((size_t)fl * (p.Dq / 8) + (line >> 4)) * toep_block_floats(p.Dq));
 }
 
