@@ -43,15 +43,13 @@ def poly_form(P, torch, dev, x, s, steps: int, n_lambda: int = 16, frames: int =
         plan.step(xi, *out)
     torch.cuda.synchronize(dev)
     fs = frames * steps / (time.perf_counter() - t0)
-    fl = nominal_flops(sp)["path"]
+    fl = toeplitz_flops(sp)["path"]
     a = fl * fs / 1e12
-    print(f"# polychromatic {n_lambda} wavelengths: {fs:.0f} frames/s ({a:.1f} TFLOP/s nominal)",
+    print(f"# polychromatic {n_lambda} wavelengths: {fs:.0f} frames/s ({a:.1f} matrix TFLOP/s)",
           file=sys.stderr, flush=True)
     return {"value": round(fs, 1), "unit": "frames/s",
             "workload": f"160 px sensor, {n_lambda} wavelengths over 600-900 nm, {frames} frames per step",
-            "roofline_path": {"bound": "alu", "achieved": round(a, 2), "peak": FP32_PEAK_TFLOPS,
-                              "unit": "TFLOP/s", "frac": round(a / FP32_PEAK_TFLOPS, 4),
-                              "flops_per_frame": fl}}
+            "roofline_path": matrix_roofline(a, {"flops_per_frame": fl})}
 
 
 FP32_PEAK_TFLOPS = 157.3     # MI355X published FP32 vector peak
@@ -86,6 +84,26 @@ def mfma_flops(s, terms: int) -> dict:
     g1 = L * n_a * 2 * Nc * D * Kp * 2.0 * terms
     g2 = L * s.n_mod * 2 * Nc * Nc * Kp * 2.0 * terms
     return {"stage1": g1, "stage2": g2}
+
+
+def toeplitz_flops(s) -> dict:
+    """Matrix-core flops per frame of the real Toeplitz form, which sensors of
+    the image windows take in FP32 and the split precisions: per axis, line and
+    part (re, im) two windows x two parities of D/2 x D/2 real products, three
+    split products each, 2 flops per multiply-add.  A double roof runs the rows
+    of one arm and the columns of the other over D lines."""
+    from workloads import FLAG_DOUBLE_ROOF
+    D, L = s.n_pupil, len(s.lambdas_nm)
+    line = 2 * 4 * (D // 2) ** 2 * 2.0 * 3
+    n_a = s.n_mod // 2 + 1 if s.n_mod > 1 else 1
+    rows, cols = L * n_a * D * line, L * s.n_mod * (D if s.flags & FLAG_DOUBLE_ROOF else 2 * D) * line
+    return {"rows": rows, "cols": cols, "path": rows + cols}
+
+
+def matrix_roofline(achieved, flops, **kw) -> dict:
+    peak = MFMA_PEAK_TFLOPS["fp16"]
+    return {"bound": "mfma", "achieved": round(achieved, 2) if achieved else None, "peak": peak, "unit": "TFLOP/s",
+            "frac": round(achieved / peak, 4) if achieved else None, **flops, **kw}
 
 
 def time_form(P, torch, s, x, n_frames, steps, warmup, ref_I, ref_S, dev, stream, label, terms, dtype, refs=None):
@@ -123,9 +141,9 @@ def time_form(P, torch, s, x, n_frames, steps, warmup, ref_I, ref_S, dev, stream
     sa = S.double()[:, :, valid]
     sb = ref_S.double()[:, :, valid]
     se = ((sa - sb).norm() / sb.norm()).item()
-    fl = mfma_flops(s, terms)
+    flops = mfma_flops(s, terms)["stage2"] if terms == 1 else toeplitz_flops(s)["cols"]
     frames = n_frames * steps
-    ach = fl["stage2"] * frames / (g2_ms / 1e3) / 1e12 if g2_ms > 0 else None
+    ach = flops * frames / (g2_ms / 1e3) / 1e12 if g2_ms > 0 else None
     peak = MFMA_PEAK_TFLOPS[dtype]
     ev = oracle_errors(torch, I, S, s, refs) if refs is not None else None
     out = {"value": round(n_frames / med, 2), "unit": "frames/s", "median_step_ms": round(med * 1e3, 4),
@@ -133,10 +151,12 @@ def time_form(P, torch, s, x, n_frames, steps, warmup, ref_I, ref_S, dev, stream
            "errors_vs_oracle": ev,
            "at_stated_error": (ev["slope_rel_rms"] <= 1e-3) if ev else None,
            "intensity_rel_err_max_vs_fp32": ie, "slope_rel_rms_vs_fp32": se,
-           "roofline": {"kernel": "k_mfma_cols_ws (stage 2: e_k = Qy_k T, |e|^2 accumulate)", "bound": "mfma",
+           "roofline": {"kernel": ("k_mfma_cols_ws (stage 2: e_k = Qy_k T, |e|^2 accumulate)" if terms == 1 else
+                                   "k_toep_cols (columns as real Toeplitz products, |e|^2 accumulate)"),
+                        "bound": "mfma",
                         "achieved": round(ach, 2) if ach else None, "peak": peak, "unit": "TFLOP/s",
                         "frac": round(ach / peak, 4) if ach else None, "traffic": None,
-                        "avg_launch_ms": round(g2_ms / max(1, g2_n), 4), "flops_per_frame": fl["stage2"]},
+                        "avg_launch_ms": round(g2_ms / max(1, g2_n), 4), "flops_per_frame": flops},
            "stage1_ms_per_step": round(g1_ms / steps, 3), "stage2_ms_per_step": round(g2_ms / steps, 3)}
     plan.close()
     print(f"# {label}: {out['value']:.0f} frames/s, vs fp32: intensity {ie:.2e}, slopes {se:.2e}; vs oracle: "
@@ -292,13 +312,12 @@ def roof_form(P, torch, dev, x, s, steps: int):
         plan.step(x, *out)
     torch.cuda.synchronize(dev)
     fs = F * steps / (time.perf_counter() - t0)
-    fl = nominal_flops(s)["path"]
+    fl = toeplitz_flops(sr)["path"]
     a = fl * fs / 1e12
-    print(f"# double roof: {fs:.0f} frames/s ({a:.1f} TFLOP/s nominal)", file=sys.stderr, flush=True)
+    print(f"# double roof: {fs:.0f} frames/s ({a:.1f} matrix TFLOP/s)", file=sys.stderr, flush=True)
     return {"value": round(fs, 1), "unit": "frames/s",
             "workload": "160 px double roof, N=512, 48 points, 40x40, 1000 frames per step",
-            "roofline_path": {"bound": "alu", "achieved": round(a, 2), "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                              "frac": round(a / FP32_PEAK_TFLOPS, 4), "flops_per_frame": fl}}
+            "roofline_path": matrix_roofline(a, {"flops_per_frame": fl})}
 
 
 def soul_form(P, torch, dev, stream, steps: int, frames: int = 1000, distinct: int = 200):
@@ -405,7 +424,7 @@ def loop_form(torch, dev, steps: int = 2000):
         st.fill_(t)
         o = P.layers(loop.screens, loop.layer_params, s.n_pupil, st).cpu().numpy()[pupil]
         opn.append(float(np.sqrt(np.mean((o - o.mean()) ** 2))))
-    fl = nominal_flops(s)["path"]
+    fl = toeplitz_flops(s)["path"]
     ach = fl / dt / 1e12
     print(f"# closed loop: {1.0 / dt:.0f} timesteps/s ({dt * 1e3:.3f} ms), residual {np.mean(closed):.0f} nm "
           f"(open loop {np.mean(opn):.0f} nm)", file=sys.stderr, flush=True)
@@ -414,9 +433,8 @@ def loop_form(torch, dev, steps: int = 2000):
             "residual_rms_nm": round(float(np.mean(closed)), 1), "open_loop_rms_nm": round(float(np.mean(opn)), 1),
             "what": "layers + mirror GEMM + sensor (1 frame) + slopes + reconstructor GEMM + integrator, "
                     "one HIP graph replay per timestep",
-            "roofline": {"kernel": "whole timestep (sensor flops at one frame per launch)", "bound": "alu",
-                         "achieved": round(ach, 2), "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                         "frac": round(ach / FP32_PEAK_TFLOPS, 4), "flops_per_timestep": fl, "traffic": None}}
+            "roofline": matrix_roofline(ach, {"flops_per_timestep": fl}, traffic=None,
+                                        kernel="whole timestep (sensor flops at one frame per launch)")}
 
 
 def sh_form(P, torch, dev, x, steps: int):
@@ -426,7 +444,7 @@ def sh_form(P, torch, dev, x, steps: int):
     240 x 240 samples, 16 x 16 pixels) over 100 frames (six LGS sensors per
     timestep), and the SCAO shape as a polychromatic sensor (Table 4) over
     three wavelengths.  Centre-of-gravity slopes; flops are those the kernel executes
-    (two complex products per subaperture, |F|^2)."""
+    (two products folded by conjugate symmetry per subaperture, |F|^2)."""
     import numpy as np
     from workloads import von_karman_opd
 
@@ -441,7 +459,8 @@ def sh_form(P, torch, dev, x, steps: int):
         torch.cuda.synchronize(dev)
         dt = (time.perf_counter() - t0) / reps
         b, M = desc.n_pupil // desc.n_subap, desc.n_fft
-        fl = (8.0 * b * b * M + 8.0 * b * M * M + 3.0 * M * M) * sh.n_valid
+        h, m = (b + 1) // 2, (M + 1) // 2
+        fl = (16.0 * h * h * m + (8.0 * h + 12.0) * m * M) * sh.n_valid
         return int(opd.shape[0]) / dt, fl, sh.n_valid
 
     fs1, fl1, nv1 = one(P.sh_desc(160, 20, 56, 7, 0.0, 750.0), x, steps)
@@ -492,7 +511,7 @@ def hetero_form(P, torch, dev, stream, steps: int, graph_reps: int = 200):
     for c in tune.get("tried", []):
         name = {P.MODE_LAUNCHES: "launches", P.MODE_PERSISTENT: "persistent"}.get(c["mode"], str(c["mode"]))
         best_by_mode[name] = round(min(best_by_mode.get(name, c["ms"]), c["ms"]), 3)
-    path = sum(nominal_flops(s)["path"] for s in w.sensors)
+    path = sum(toeplitz_flops(s)["path"] for s in w.sensors)
 
     def timed():
         """Timesteps/s over ``steps`` steps, then the kernel durations of one
@@ -525,7 +544,7 @@ def hetero_form(P, torch, dev, stream, steps: int, graph_reps: int = 200):
         pdt, pkms, pach = timed()
         persistent = {"value": round(F * steps / pdt, 2), "unit": "timesteps/s",
                       "tuning": {k: pb[k] for k in ("chunk", "wg_per_cu", "row_groups", "row_tiles") if k in pb},
-                      "roofline_frac": round(pach / FP32_PEAK_TFLOPS, 4),
+                      "roofline_frac": round(pach / MFMA_PEAK_TFLOPS["fp16"], 4),
                       "kernel_ms_per_step": {k: round(v[0], 3) for k, v in pkms.items() if v[1]},
                       "launches_per_step": sum(v[1] for v in pkms.values())}
         plan.set_tuning(**{k: tune[k] for k in ("mode", "chunk", "wg_per_cu", "row_groups")})
@@ -561,10 +580,9 @@ def hetero_form(P, torch, dev, stream, steps: int, graph_reps: int = 200):
             "best_ms_by_mode": best_by_mode,
             "persistent": persistent,
             "graph_timestep_ms": round(lat, 4), "graph_replay_matches_eager": same,
-            "roofline": {"bound": "alu", "achieved": round(ach, 2), "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                         "frac": round(ach / FP32_PEAK_TFLOPS, 4), "flops_per_timestep": path, "traffic": None,
-                         "kernel_ms_per_step": {k: round(v[0], 3) for k, v in kms.items() if v[1]},
-                         "launches_per_step": sum(v[1] for v in kms.values())}}
+            "roofline": matrix_roofline(ach, {"flops_per_timestep": path}, traffic=None,
+                                        kernel_ms_per_step={k: round(v[0], 3) for k, v in kms.items() if v[1]},
+                                        launches_per_step=sum(v[1] for v in kms.values()))}
 
 
 def measured_traffic(kernel: str, frames_per_launch: float):
@@ -769,28 +787,25 @@ def small_sensor_forms(P, torch, dev, stream, reps: int) -> dict:
                                                "FETCH_SIZE/WRITE_SIZE)",
                                "algorithmic_bytes": 4.0 * F * (sp.n_pupil ** 2 + 4 * sp.n_pupil ** 2)}
         elif prec == 0:
-            fl = nominal_flops(sp)
+            fl = toeplitz_flops(sp)
             cms, cn = kern["cols"]
             fpl = F * reps / max(1, cn)
             ach = fl["cols"] * fpl / (cms / max(1, cn) / 1e3) / 1e12 if cms > 0 else None
-            rec["roofline"] = {"kernel": "k_cols (column pass)", "bound": "alu", "achieved": round(ach, 2),
-                               "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(ach / FP32_PEAK_TFLOPS, 4),
-                               "flops_per_frame": fl["cols"], "frames_per_launch": fpl,
-                               "avg_launch_ms": round(cms / max(1, cn), 4), "traffic": None}
+            rec["roofline"] = matrix_roofline(ach, {"flops_per_frame": fl["cols"]}, frames_per_launch=fpl,
+                                              kernel="k_toep_cols (columns as real Toeplitz products)",
+                                              avg_launch_ms=round(cms / max(1, cn), 4), traffic=None)
             gpu_ms = sum(v[0] for v in kern.values()) / reps
-            rec["roofline_path"] = {"achieved": round(fl["path"] * F / (gpu_ms / 1e3) / 1e12, 2),
-                                    "frac": round(fl["path"] * F / (gpu_ms / 1e3) / 1e12 / FP32_PEAK_TFLOPS, 4),
-                                    "flops_per_frame": fl["path"], "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s"}
+            rec["roofline_path"] = matrix_roofline(fl["path"] * F / (gpu_ms / 1e3) / 1e12,
+                                                   {"flops_per_frame": fl["path"]})
         else:
             terms = 1 if prec in (PREC_BF16, PREC_FP16) else 3
-            fl = mfma_flops(sp, terms)
+            flops = mfma_flops(sp, terms)["stage2"] if terms == 1 else toeplitz_flops(sp)["cols"]
             g2, n2 = kern["mfma"]
             fpl = F * reps / max(1, n2)
-            ach = fl["stage2"] * fpl / (g2 / max(1, n2) / 1e3) / 1e12 if g2 > 0 else None
-            rec["roofline"] = {"kernel": "k_mfma_cols_ws (stage 2)", "bound": "mfma",
-                               "achieved": round(ach, 2) if ach else None, "peak": MFMA_PEAK_TFLOPS["bf16"],
-                               "unit": "TFLOP/s", "frac": round(ach / MFMA_PEAK_TFLOPS["bf16"], 4) if ach else None,
-                               "flops_per_frame": fl["stage2"], "traffic": None}
+            ach = flops * fpl / (g2 / max(1, n2) / 1e3) / 1e12 if g2 > 0 else None
+            rec["roofline"] = matrix_roofline(ach, {"flops_per_frame": flops}, traffic=None,
+                                              kernel="k_mfma_cols_ws (stage 2)" if terms == 1 else
+                                              "k_toep_cols (columns as real Toeplitz products)")
             rec["at_stated_error"] = err["slope_rel_rms"] <= 1e-3
         out[label] = rec
         plan.close()
@@ -938,7 +953,7 @@ def main() -> int:
 
     frames = w.n_frames * args.steps
     value = frames / dt
-    flops = nominal_flops(s)
+    flops = toeplitz_flops(s)
     host = host_info(torch, dev)
     cols_ms, cols_n = kern["cols"]
     frames_per_launch = w.n_frames * args.steps / max(1, cols_n)
@@ -961,33 +976,24 @@ def main() -> int:
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32",
+        "arithmetic": "float32 operands as fp16 hi and lo parts (22 significand bits), three matrix products, "
+                      "float32 sums",
         "data": "synthetic von Karman screens (r0 0.12 m, L0 40 m) + 5 mas tip/tilt jitter, seeds 2/12",
         "errors_vs_oracle": fp32_err,
         "host": host,
         "config": {"workload": w.name, "frames_per_step": w.n_frames, "n_pupil": s.n_pupil, "n_fft": s.n_fft,
                    "n_mod": s.n_mod, "n_subap": s.n_subap, "obstruction": s.obstruction,
                    "lambda_nm": s.lambdas_nm[0], "precision": "fp32", "intensity": "pupil-image windows"},
-        "roofline": {
-            "kernel": "k_cols (column pass: column FFT, mask, column IFFT, |e|^2 accumulate)",
-            "bound": "alu",
-            "achieved": round(achieved, 3),
-            "peak": FP32_PEAK_TFLOPS,
-            "unit": "TFLOP/s",
-            "frac": round(achieved / FP32_PEAK_TFLOPS, 4),
-            "traffic": measured_traffic("k_cols", frames_per_launch),
-            "traffic_unit": "bytes per launch (HBM, rocprofv3 FETCH_SIZE/WRITE_SIZE, copy-calibrated)",
-            "launches": cols_n,
-            "avg_launch_ms": round(cols_ms / max(1, cols_n), 4),
-            "frames_per_launch": frames_per_launch,
-            "flops_per_frame": flops["cols"],
-        },
-        "roofline_path": {
-            "achieved": round(flops["path"] * frames / (gpu_ms / 1e3) / 1e12, 3),
-            "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-            "frac": round(flops["path"] * frames / (gpu_ms / 1e3) / 1e12 / FP32_PEAK_TFLOPS, 4),
-            "flops_per_frame": flops["path"],
-            "kernel_ms": {k: round(v[0], 3) for k, v in kern.items()},
-        },
+        "roofline": matrix_roofline(
+            achieved, {"flops_per_frame": flops["cols"]},
+            kernel="k_toep_cols (columns as real Toeplitz products on fp16 hi/lo parts, |e|^2 accumulate)",
+            traffic=measured_traffic("k_toep_cols", frames_per_launch),
+            traffic_unit="bytes per launch (HBM, rocprofv3 FETCH_SIZE/WRITE_SIZE, copy-calibrated)",
+            launches=cols_n, avg_launch_ms=round(cols_ms / max(1, cols_n), 4), frames_per_launch=frames_per_launch),
+        "roofline_path": matrix_roofline(
+            flops["path"] * frames / (gpu_ms / 1e3) / 1e12, {"flops_per_frame": flops["path"]},
+            nominal_fft_tflops=round(nominal_flops(s)["path"] * frames / (gpu_ms / 1e3) / 1e12, 3),
+            kernel_ms={k: round(v[0], 3) for k, v in kern.items()}),
         "graph_timestep": {"ms": round(graph_ms, 4), "frames_per_s": round(1e3 / graph_ms, 1),
                            "replay_matches_batched": graph_ok,
                            "what": "one frame (forward + slopes) per HIP graph replay, median of 200"},
