@@ -65,7 +65,7 @@ struct ShArgs {
   const uint8_t* valid;    // [n][n]
   float* pixels;           // [frames][n][n][k][k] or nullptr
   float* slopes;           // [frames][2][n][n]
-  int D, n, b, M, r, k, n_lam;
+  int D, n, b, M, r, k, n_lam, tpp_log2;
   float wnorm[PWFS_MAX_LAMBDA];             // w_l s_l^2 / (M^2 sum A^2) (monochromatic: 1 / (M^2 sum A^2))
   double four_over_lam[PWFS_MAX_LAMBDA];
 };
@@ -97,11 +97,14 @@ size_t sh_lds(int b, int M, int k, int nt) {
 // columns (r >= 4 tpp), for H <= 4.  NT = 128 where the pairs fill no more (the
 // 8 x 8 pixels of 56 samples).  Bound by vector issue: 4 H + 8 instructions per
 // two samples, where the unfolded complex products took 8 b + 4.  68 x 68
-// subapertures of 7 pixels onto 240 x 240, 10 frames: 1298 -> 524 us; 20 x 20 of
-// 8 pixels onto 56 x 56, 500 frames: 655 -> 331 us.
+// subapertures of 7 pixels onto 240 x 240, 10 frames: 1270 -> 510 us; 20 x 20 of
+// 8 pixels onto 56 x 56, 500 frames: 655 -> 290 us.
 template <int H, int NC, int NT>
 __global__ __launch_bounds__(NT) void k_sh(ShArgs p) {
   extern __shared__ float4 sh_mem[];
+  // i / d for 0 <= i < 2^18, d <= 512, by the reciprocal (the quotient's distance
+  // to an integer is at least 1 / (2 d)): an integer division is 25 instructions
+  auto quot = [](int i, float inv) { return (int)(((float)i + 0.5f) * inv); };
   const int tid = threadIdx.x;
   const int sub = blockIdx.x % (p.n * p.n), f = blockIdx.x / (p.n * p.n);
   const int si = sub / p.n, sj = sub % p.n;
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(NT) void k_sh(ShArgs p) {
   for (int l = 0; l < p.n_lam; ++l) {
     for (int i = tid; i < hm * H; i += NT) sC[(i / H) * CW + i % H] = p.W[(size_t)l * hm * H + i];
     for (int i = tid; i < b * b; i += NT) {
-      const int y = i / b, x = i % b;
+      const int y = b == 2 * H ? i / (2 * H) : i / (2 * H - 1), x = i - y * b;
       const size_t g = (size_t)(si * b + y) * p.D + sj * b + x;
       float sn, cs;
       sincos_quarters((double)opd[g] * p.four_over_lam[l], sn, cs);
@@ -159,8 +162,9 @@ __global__ __launch_bounds__(NT) void k_sh(ShArgs p) {
     }
     __syncthreads();
     // T+-[y][u], T+-[y][M-1-u]
+    const float inv_hm = 1.f / (float)hm, inv_k = 1.f / (float)k;
     for (int i = tid; i < H * hm; i += NT) {
-      const int y = i / hm, u = i - y * hm;
+      const int y = quot(i, inv_hm), u = i - y * hm;
       const float2* w = sC + u * CW;
       const float4* e = sF + 2 * H * y;
       float cr = 0.f, ci = 0.f, sr = 0.f, sii = 0.f, dr = 0.f, di = 0.f, tr = 0.f, ti = 0.f;
@@ -187,11 +191,11 @@ __global__ __launch_bounds__(NT) void k_sh(ShArgs p) {
     // sums; with k odd the middle pixel row is its own pair, over half its rows,
     // and the middle v of an odd M is its own mirror image.
     const int pairs = sh_half(k) * k;
-    const int tpp = sh_tpp(pairs, r);
+    const int tpp = 1 << p.tpp_log2;
     for (int base = 0; base < pairs * tpp; base += NT) {
       const int slot = base + tid;
-      const int P = slot / tpp, s = slot - P * tpp;
-      const int pr = P / k, pc = P - pr * k;
+      const int P = slot >> p.tpp_log2, s = slot - (P << p.tpp_log2);
+      const int pr = quot(P, inv_k), pc = P - pr * k;
       const bool mid = 2 * pr == k - 1;
       float acc1 = 0.f, acc2 = 0.f;
       if (P < pairs) {
@@ -259,8 +263,9 @@ __global__ __launch_bounds__(NT) void k_sh(ShArgs p) {
   for (int P = tid; P < kk; P += 64) {
     const float v = sP[P];
     t0 += v;
-    tx = fmaf(v, (float)(P % k) - c0, tx);
-    ty = fmaf(v, (float)(P / k) - c0, ty);
+    const int py = quot(P, 1.f / (float)k);
+    tx = fmaf(v, (float)(P - py * k) - c0, tx);
+    ty = fmaf(v, (float)py - c0, ty);
     if (pix_out) pix_out[P] = v;
   }
 #pragma unroll
@@ -305,6 +310,7 @@ struct pwfs_sh_s {
   uint8_t* valid = nullptr;
   size_t lds = 0;
   bool narrow = false;   // 128 threads
+  int tpp_log2 = 0;
   int cols = 1;          // focal columns of a pixel per thread
 };
 
@@ -419,6 +425,7 @@ extern "C" int pwfs_sh_plan(const pwfs_sh_desc* d, int max_frames, void* ws, siz
   p += a256(sizeof(float2) * nl * M * b);
   s->valid = (uint8_t*)p;
   const int pairs = sh_half(s->k) * s->k, tpp = sh_tpp(pairs, s->r);
+  while ((1 << s->tpp_log2) < tpp) ++s->tpp_log2;
   s->narrow = pairs * tpp <= 128;
   s->cols = s->r / tpp;
   s->lds = sh_lds(b, M, s->k, s->narrow ? 128 : kShBlock);
@@ -456,6 +463,7 @@ extern "C" int pwfs_sh_forward(pwfs_sh_t s, const float* opd, int nf, float* pix
   a.r = s->r;
   a.k = s->k;
   a.n_lam = s->n_lam;
+  a.tpp_log2 = s->tpp_log2;
   for (int l = 0; l < s->n_lam; ++l) {
     a.wnorm[l] = s->wnorm[l];
     a.four_over_lam[l] = s->four_over_lam[l];
