@@ -76,7 +76,7 @@ struct Prof;
 int forward_mfma(const SensorPlan& sp, const float* opd, long long opd_stride, float* out, long long out_stride,
                  int nf, void* scratch, hipStream_t st, Prof* prof);
 
-// Toeplitz form on the matrix cores (pwfs_toep.hip)
+// Toeplitz form on the matrix cores (toep_forward.hpp)
 bool toep_eligible(const pwfs_sensor_desc& d);
 size_t toep_table_bytes(const pwfs_sensor_desc& d);
 size_t toep_scratch_frame_bytes(const pwfs_sensor_desc& d);
