@@ -428,8 +428,12 @@ struct SplitPair {
   SplitArgs s[2];
 };
 
-// A thread takes four columns of a row (one 16-byte load where the rows allow
-// it), or, with a transpose, four rows of a column: 8-byte stores into the
+// four floats in one access of 4-byte alignment (rows of any length)
+struct __attribute__((packed, aligned(4))) Float4 {
+  float v[4];
+};
+
+// A thread takes four columns of a row in one load, or, with a transpose, four rows of a column: 8-byte stores into the
 // transpose, 2-byte ones side by side into the rows.
 __global__ __launch_bounds__(256) void k_split(SplitPair a) {
   const bool second = blockIdx.x >= a.s[0].wgs;
@@ -453,10 +457,10 @@ __global__ __launch_bounds__(256) void k_split(SplitPair a) {
   const int k = 4 * (int)(i - r * per);
   if (r >= p.rows) return;
   const float* src = p.src + r * p.ld + k;
-  if (k + 4 <= p.cols && ((uintptr_t)src & 15) == 0) {
-    const f32x4_t x = *(const f32x4_t*)src;
+  if (k + 4 <= p.cols) {
+    const Float4 x = *(const Float4*)src;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = x[q] * p.scale;
+    for (int q = 0; q < 4; ++q) v[q] = x.v[q] * p.scale;
   } else {
 #pragma unroll
     for (int q = 0; q < 4; ++q) v[q] = k + q < p.cols ? src[q] * p.scale : 0.f;
@@ -563,7 +567,7 @@ struct ParamCopyBatch {
   unsigned first[kMaxSegments + 1];
   int n;
 };
-// a thread copies four columns of a row, in 16 bytes where both rows allow it
+// a thread copies four columns of a row in one access
 __global__ __launch_bounds__(256) void k_copy2d(ParamCopyBatch b) {
   int t = 0;
   while (t + 1 < b.n && blockIdx.x >= b.first[t + 1]) ++t;
@@ -573,8 +577,8 @@ __global__ __launch_bounds__(256) void k_copy2d(ParamCopyBatch b) {
   if (r >= p.rows) return;
   const float* src = p.src + (long long)r * p.src_ld + c;
   float* dst = p.dst + (long long)r * p.dst_ld + c;
-  if (c + 4 <= p.cols && (((uintptr_t)src | (uintptr_t)dst) & 15) == 0) {
-    *(f32x4_t*)dst = *(const f32x4_t*)src;
+  if (c + 4 <= p.cols) {
+    *(Float4*)dst = *(const Float4*)src;
   } else {
     for (int q = 0; q < 4 && c + q < p.cols; ++q) dst[q] = src[q];
   }
@@ -650,11 +654,12 @@ int gemm_ws_launch(const GemmArgs& a0, hipStream_t st) {
 // workgroups on the chip (one per CU) and no loss epilogue take the
 // wave-specialised tiles: 128 x 256 where that still gives four rounds,
 // else 128 x 128.  The rest (two-plane products, the loss and gradient
-// epilogues) take the 256-lane tiles, and so do hidden layers on 128 x 128
-// tiles: two workgroups share a CU there, and the GELU of one (43 us of vector
+// epilogues) take the 256-lane tiles, and so do hidden layers of at least two
+// rounds of them (two workgroups share a CU): the GELU of one (43 us of vector
 // issue for 20000 x 1024) runs beside the products of the other (a prediction of
-// 20000 samples: 440 us, 451 us wave-specialised).
-constexpr int kWsMinTiles = 512, kWsWideTiles = 1024;
+// 20000 samples: 440 us, 451 us wave-specialised; with 664 tiles, 1.3 rounds,
+// the wave-specialised ones are 1 % faster).
+constexpr int kWsMinTiles = 512, kWsWideTiles = 1024, kSharedMinTiles = 1024;
 
 // Products of fewer 128 x 128 tiles than two rounds of the chip take 64 x 64
 // tiles (training products of 64 to 200 tiles: 64 us -> 25 to 36 us).  Two-plane
@@ -679,7 +684,8 @@ int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
   if constexpr (EPI != E_DHIDDEN && EPI != E_OUTPUT) {
     const long long mt = (a.M + kGemmTile - 1) / kGemmTile;
     if (mt * ((a.N + 255) / 256) >= kWsWideTiles) return gemm_ws_launch<EPI, 256>(a, st);
-    if (EPI != E_HIDDEN && mt * ((a.N + 127) / 128) >= kWsMinTiles) return gemm_ws_launch<EPI, 128>(a, st);
+    const long long tiles = mt * ((a.N + 127) / 128);
+    if (tiles >= kWsMinTiles && !(EPI == E_HIDDEN && tiles >= kSharedMinTiles)) return gemm_ws_launch<EPI, 128>(a, st);
   }
   return gemm_launch<1, EPI, 64>(a, st);
 }
