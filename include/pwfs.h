@@ -205,7 +205,8 @@ int pwfs_slopes(pwfs_plan_t plan, const float* d_intensity, int n_frames, float*
  *             and the intensity on chip, so a frame reads only its OPD from
  *             HBM and writes only its intensity; the |e|^2 sum runs in point
  *             order, so results match the other modes to rounding, not bits.
- *  chunk      frames per pass, 1 .. max_chunk (set by the workspace size)
+ *  chunk      frames per pass, 1 .. max_chunk; fewer where the workspace's
+ *             scratch holds fewer
  *  wg_per_cu  persistent workgroups per compute unit, 1 .. 8
  *  row_groups minimum number of row-pass work items per pass
  *  spin_limit polls of a persistent pass's dependency wait before it gives

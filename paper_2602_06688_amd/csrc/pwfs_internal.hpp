@@ -49,7 +49,8 @@ struct Layout {
   std::vector<size_t> offsets;  // [sensor][region]
   std::vector<size_t> sensor_rbuf;
   size_t rbuf_offset = 0, rbuf_bytes = 0, counters_offset = 0, total = 0;
-  int chunk = 1;
+  int chunk = 1;       // frames per pass that the scratch holds
+  int max_chunk = 1;   // frames per pass that a tuning may ask for
 };
 
 struct TiltPoint {
@@ -116,7 +117,8 @@ struct Prof {
 
 struct pwfs_plan_s {
   std::vector<pwfs::SensorPlan> s;
-  int max_frames = 0, chunk = 1, max_chunk = 1, n_cu = 256;
+  int max_frames = 0, n_cu = 256;
+  int chunk = 1, pass = 1, max_chunk = 1;   // frames per pass: now, at most, accepted in a tuning
   pwfs_tuning tune{};
   int* counters = nullptr;      // persistent-pass claim and dependency counters
   size_t opd_stride = 0, int_stride = 0, slope_stride = 0;

@@ -272,11 +272,13 @@ static void sensor_regions(const pwfs_sensor_desc& d, size_t out[kRegions]) {
 
 // per frame: the row-pass output [n_lam][n_a][Nc][Dp], then the pupil field
 // [n_lam][D][D] (the field block of a pass sits after all frames' R blocks)
-size_t rbuf_frame_bytes(const pwfs_sensor_desc& d) {
+size_t dense_frame_bytes(const pwfs_sensor_desc& d) {   // of the FFT and dense forms
   const Geometry g = geometry(d);
-  if (toep_eligible(d)) return toep_scratch_frame_bytes(d);
   if (d.precision != PWFS_FP32) return mfma_scratch_frame_bytes(d);
   return sizeof(float2) * ((size_t)g.n_lam * g.n_a * g.Nc * g.Dp + (size_t)g.n_lam * g.D * g.D);
+}
+size_t rbuf_frame_bytes(const pwfs_sensor_desc& d) {
+  return toep_eligible(d) ? toep_scratch_frame_bytes(d) : dense_frame_bytes(d);
 }
 
 // float2 offset of the field block of a pass of nf frames
@@ -285,7 +287,12 @@ size_t rbuf_field_offset(const pwfs_sensor_desc& d, int nf) {
   return (size_t)nf * g.n_lam * g.n_a * g.Nc * g.Dp;
 }
 
-int choose_chunk(const pwfs_sensor_desc* s, int n, int max_frames) {
+// Frames per pass: those the scratch is laid out for, or, with `accepted`, those
+// a tuning may ask for.  The two differ where the 12 GiB cap binds and the
+// Toeplitz form's scratch takes more per frame than the sensor's FFT or dense
+// form: a tuning saved with a pass size of that form stays valid, and its passes
+// are as large as the scratch holds.
+int choose_chunk(const pwfs_sensor_desc* s, int n, int max_frames, bool accepted) {
   // enough frames per pass that a launch's tail is a small part of it: >= ~16384
   // workgroups of the FFT or matrix-core column pass (16 rounds of the chip's
   // resident workgroups) or four rounds of the Toeplitz column pass, which
@@ -295,7 +302,7 @@ int choose_chunk(const pwfs_sensor_desc* s, int n, int max_frames) {
   int want = 1;
   for (int i = 0; i < n; ++i) {
     const Geometry g = geometry(s[i]);
-    per += rbuf_frame_bytes(s[i]);
+    per += accepted ? std::min(rbuf_frame_bytes(s[i]), dense_frame_bytes(s[i])) : rbuf_frame_bytes(s[i]);
     if (toep_eligible(s[i])) want = std::max(want, toep_frames_per_pass(s[i]));
     int colwg;
     if (s[i].precision == PWFS_FP32) {
@@ -313,8 +320,8 @@ int choose_chunk(const pwfs_sensor_desc* s, int n, int max_frames) {
 }
 
 // frames per pass of a new plan: passes of equal size
-int equal_chunk(int max_chunk, int max_frames) {
-  const int passes = (max_frames + max_chunk - 1) / max_chunk;
+int equal_chunk(int pass, int max_frames) {
+  const int passes = (max_frames + pass - 1) / pass;
   return (max_frames + passes - 1) / passes;
 }
 
@@ -343,7 +350,8 @@ int fft_lanes(int N) {
 int layout(const pwfs_sensor_desc* s, int n, int max_frames, Layout* L) {
   size_t off = 0;
   L->offsets.assign((size_t)n * kRegions, 0);
-  L->chunk = choose_chunk(s, n, max_frames);
+  L->chunk = choose_chunk(s, n, max_frames, false);
+  L->max_chunk = choose_chunk(s, n, max_frames, true);
   // a Toeplitz sensor's reference intensity is needed while its plan is built
   // only: it sits behind one frame's scratch where a pass has more frames
   std::vector<size_t> one(n, 0);
@@ -1046,12 +1054,13 @@ int pwfs_plan(const pwfs_sensor_desc* s, int n, int max_frames, void* ws, size_t
   if (!p) return fail(PWFS_EINVAL, "out of host memory");
   p->max_frames = max_frames;
   p->chunk = equal_chunk(L.chunk, max_frames);
-  p->max_chunk = L.chunk;
+  p->pass = L.chunk;
+  p->max_chunk = L.max_chunk;
   p->tune.mode = PWFS_MODE_LAUNCHES;
   p->tune.chunk = p->chunk;
   p->tune.wg_per_cu = 2;
   p->tune.row_groups = 2048;
-  p->tune.max_chunk = L.chunk;
+  p->tune.max_chunk = L.max_chunk;
   p->ws = (char*)ws;
   p->ws_bytes = ws_bytes;
   p->rbuf = (float2*)((char*)ws + L.rbuf_offset);
@@ -1158,7 +1167,7 @@ int pwfs_set_tuning(pwfs_plan_t p, const pwfs_tuning* t) {
   if (t->mode != PWFS_MODE_LAUNCHES && t->mode != PWFS_MODE_PERSISTENT && t->mode != PWFS_MODE_FUSED)
     return fail(PWFS_EINVAL, "unknown mode");
   if (t->chunk < 1 || t->chunk > p->max_chunk)
-    return fail(PWFS_EINVAL, "chunk must be in [1, %d] (the workspace's pass size)", p->max_chunk);
+    return fail(PWFS_EINVAL, "chunk must be in [1, %d]", p->max_chunk);
   if (t->wg_per_cu < 1 || t->wg_per_cu > 8) return fail(PWFS_EINVAL, "wg_per_cu must be in [1, 8]");
   if (t->row_groups < 1 || t->row_groups > (1 << 20)) return fail(PWFS_EINVAL, "row_groups out of range");
   if (t->reserved[0] != 0 || t->reserved[1] != 0) return fail(PWFS_EINVAL, "reserved fields must be 0");
@@ -1176,7 +1185,7 @@ int pwfs_set_tuning(pwfs_plan_t p, const pwfs_tuning* t) {
   }
   p->tune = *t;
   p->tune.max_chunk = p->max_chunk;
-  p->chunk = t->chunk;
+  p->chunk = std::min((int)t->chunk, p->pass);
   return PWFS_OK;
 }
 

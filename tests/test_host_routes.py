@@ -1,0 +1,58 @@
+"""Which launches a plan makes, and that they stay inside its scratch: host code
+of the built library alone (tests/host_routes.py), no GPU."""
+
+import pytest
+
+import host_routes
+from workloads import FLAG_DOUBLE_ROOF, FLAG_REF_SLOPES, PREC_BF16X3, PREC_FP16X3, PREC_FP32, tiny_sensor
+
+
+@pytest.fixture(scope="module")
+def host():
+    exe = host_routes.build()
+    if exe is None:
+        pytest.skip("hipcc or the built library not available")
+    h = host_routes.Host(exe)
+    yield h
+    h.close()
+
+
+def _sensor(D, N, sep, n_mod, nl=1, prec=PREC_FP32, flags=0, rings=0):
+    lams = tuple(750.0 + 10.0 * i for i in range(nl))
+    return tiny_sensor(n_pupil=D, n_fft=N, n_subap=max(1, D // 4), pupil_sep_px=float(sep), n_mod=n_mod, mod_radius_lod=3.0,
+                       lambdas_nm=lams, lambda_weights=(1.0 / nl,) * nl, lambda_ref_nm=750.0, precision=prec,
+                       flags=flags, src_rings=rings, src_radius_lod=1.0 if rings else 0.0)
+
+
+# sensor, frames, and the pass size that plans of the FFT and dense forms accept
+# for it: 12 GiB of their scratch per pass
+PASSES = [
+    (_sensor(136, 512, 336, 73, rings=2), 454, 92),
+    (_sensor(6, 128, 82, 820, nl=15, prec=PREC_FP16X3), 917, 917),
+    (_sensor(120, 512, 176, 828, prec=PREC_BF16X3), 350, 126),
+    (_sensor(244, 768, 250, 637), 986, 40),
+    (_sensor(54, 768, 364, 857, flags=FLAG_DOUBLE_ROOF), 551, 542),
+    (_sensor(62, 128, 64, 89, nl=10), 770, 446),
+    (_sensor(180, 512, 238, 37, nl=14, flags=FLAG_DOUBLE_ROOF | FLAG_REF_SLOPES), 493, 85),
+    (_sensor(234, 768, 250, 91, prec=PREC_FP16X3, flags=FLAG_REF_SLOPES), 979, 308),
+]
+
+
+@pytest.mark.parametrize("i", range(len(PASSES)))
+def test_pass_sizes_of_saved_tunings_stay_accepted(host, i):
+    """A tuning saved with the pass size that a sensor's FFT or dense form accepts
+    is accepted by the Toeplitz form too, whose scratch takes more per frame; its
+    passes are then as large as the scratch holds."""
+    s, frames, accepted = PASSES[i]
+    rc, most, _ = host.plan([s], frames)
+    assert rc == 0
+    try:
+        assert most >= accepted
+        rc, _, chunk = host.tune(0, accepted)
+        assert rc == 0 and chunk == accepted
+        rc, launches = host.forward(frames)
+        assert rc == 0
+        rows = [x for x in launches if x[0] in ("k_toep_rows", "k_toep_cols")]
+        assert rows and all(x[3] == 0 for x in rows)
+    finally:
+        host.free()
