@@ -41,13 +41,14 @@ struct SensorPlan {
   std::vector<uint8_t> valid_host;
   size_t opd_offset, int_offset, slope_offset;
   float2* rbuf = nullptr;   // this sensor's pass scratch
+  size_t rbuf_bytes = 0;
   int row_tile = 0;         // row-pass tile rows (0: the default of its N)
   bool toep = false;        // runs the Toeplitz passes (toep_eligible)
 };
 
 struct Layout {
   std::vector<size_t> offsets;  // [sensor][region]
-  std::vector<size_t> sensor_rbuf;
+  std::vector<size_t> sensor_rbuf, sensor_rbuf_bytes;
   size_t rbuf_offset = 0, rbuf_bytes = 0, counters_offset = 0, total = 0;
   int chunk = 1;       // frames per pass that the scratch holds
   int max_chunk = 1;   // frames per pass that a tuning may ask for

@@ -373,11 +373,13 @@ int layout(const pwfs_sensor_desc* s, int n, int max_frames, Layout* L) {
   // one scratch region per sensor (sensors of a persistent pass run together)
   L->rbuf_offset = off;
   L->sensor_rbuf.assign(n, 0);
+  L->sensor_rbuf_bytes.clear();
   for (int i = 0; i < n; ++i) {
     L->sensor_rbuf[i] = off;
     if (one[i]) L->offsets[(size_t)i * kRegions + R_REFINT] = off + one[i];
-    off += align256(toep_eligible(s[i]) ? toep_scratch_bytes(s[i], L->chunk)
-                                        : rbuf_frame_bytes(s[i]) * (size_t)L->chunk);
+    L->sensor_rbuf_bytes.push_back(align256(toep_eligible(s[i]) ? toep_scratch_bytes(s[i], L->chunk)
+                                                                : rbuf_frame_bytes(s[i]) * (size_t)L->chunk));
+    off += L->sensor_rbuf_bytes[i];
   }
   L->counters_offset = off;
   off += align256(sizeof(int) * 64);
@@ -1082,6 +1084,7 @@ int pwfs_plan(const pwfs_sensor_desc* s, int n, int max_frames, void* ws, size_t
     for (int a = 0; a < sp.arms; ++a) sp.arm_g[a] = arm_geometry(s[i], a);
     for (int r = 0; r < kRegions; ++r) sp.dev[r] = (char*)ws + L.offsets[(size_t)i * kRegions + r];
     sp.rbuf = (float2*)((char*)ws + L.sensor_rbuf[i]);
+    sp.rbuf_bytes = L.sensor_rbuf_bytes[i];
     std::vector<float> A;
     std::vector<uint8_t> V;
     pupil_and_valid(s[i], A, V);

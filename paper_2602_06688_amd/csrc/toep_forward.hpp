@@ -458,6 +458,16 @@ int toep_failed(hipError_t e, const char* what) {
   return PWFS_EHIP;
 }
 
+// Whether the scratch of a sensor holds `bytes`, from what a pass is about to be
+// given (the layout sized it for every pass that a plan may make).
+int toep_scratch_holds(const SensorPlan& sp, size_t bytes) {
+  if (bytes <= sp.rbuf_bytes) return PWFS_OK;
+  char msg[160];
+  snprintf(msg, sizeof msg, "a pass needs %zu bytes of scratch, the plan has %zu", bytes, sp.rbuf_bytes);
+  set_last_error(msg);
+  return PWFS_EWORKSPACE;
+}
+
 size_t toep_lds_of(int KS) {
   switch (KS) {
     case 1: return std::max(toep_lds_rows<1>(), toep_lds_cols<1>(false));
@@ -478,6 +488,13 @@ int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, f
   const Geometry& g = sp.g;
   const ToepGeom t = toep_geom(sp.desc);
   ToepPass tp = toep_pass(sp, t, opd, opd_stride, out, out_stride, nf, rbuf, 512);
+  size_t need = toep_scratch_frame_bytes(sp.desc) * (size_t)nf;
+  if (sp.ident != 1) {
+    tp.ca.n_parts = toep_parts(t, g, nf, &tp.ca.per_wg);
+    tp.ca.part = (float*)((char*)rbuf + ta256(need));
+    if (tp.ca.n_parts > 1) need = ta256(need) + toep_part_frame_bytes(t, g) * (size_t)nf;
+  }
+  if (const int rc = toep_scratch_holds(sp, need)) return rc;
   hipError_t e;
   int slot;
   // behind the pass's row output (the sums of a split pass lie behind it)
@@ -535,8 +552,6 @@ int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, f
                        st, ia);
     e = hipGetLastError();
   } else {
-    tp.ca.n_parts = toep_parts(t, g, nf, &tp.ca.per_wg);
-    tp.ca.part = (float*)((char*)rbuf + ta256(toep_scratch_frame_bytes(sp.desc) * (size_t)nf));
     e = toep_cols(t.KS, tp.ca, st);
   }
   if (e != hipSuccess) return toep_failed(e, "k_toep_cols");
@@ -554,6 +569,7 @@ int forward_toep_hetero(pwfs_plan_s* p, const std::vector<int>& which, const flo
   for (size_t i = 0; i < which.size(); ++i) {
     const SensorPlan& sp = p->s[which[i]];
     const ToepGeom t = toep_geom(sp.desc);
+    if (const int rc = toep_scratch_holds(sp, toep_scratch_frame_bytes(sp.desc) * (size_t)nf)) return rc;
     const ToepPass tp = toep_pass(sp, t, opd + sp.opd_offset + (long long)f0 * p->opd_stride,
                                   (long long)p->opd_stride, out + sp.int_offset + (long long)f0 * p->int_stride,
                                   (long long)p->int_stride, nf, sp.rbuf, p->tune.row_groups);

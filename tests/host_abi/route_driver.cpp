@@ -11,6 +11,7 @@
 //   plan <frames> <sensors> <hex description>...   -> rc max_chunk chunk
 //   tune <mode> <chunk> <row_groups>               -> rc max_chunk chunk
 //   fwd <frames>                                   -> rc launch ...
+//   scratch <sensor> <delta>                       -> bytes (its recorded size, changed by delta)
 //   free                                           -> 0
 // A launch is kernel:workgroups[:parts:over], parts the workgroups that share a
 // pair of column blocks, over the bytes past the end of the scratch.
@@ -20,6 +21,7 @@
 
 #include <sys/mman.h>
 
+#include <algorithm>
 #include <iostream>
 #include <sstream>
 #include <vector>
@@ -31,11 +33,14 @@ namespace {
 pwfs_plan_t g_plan = nullptr;
 std::vector<std::string> g_seen;
 
-// end of the scratch region that holds address p
+// end of the scratch of the sensor whose scratch starts at p: what is recorded
+// for it, at most the next sensor's or the counters
 const char* scratch_end(const void* p) {
   const char* end = (const char*)g_plan->counters;
-  for (const pwfs::SensorPlan& s : g_plan->s)
-    if ((const char*)s.rbuf > (const char*)p && (const char*)s.rbuf < end) end = (const char*)s.rbuf;
+  for (const pwfs::SensorPlan& s : g_plan->s) {
+    if ((const char*)s.rbuf > (const char*)p) end = std::min(end, (const char*)s.rbuf);
+    if ((const char*)s.rbuf == (const char*)p) end = std::min(end, (const char*)p + s.rbuf_bytes);
+  }
   return end;
 }
 long long over(const void* base, const void* end) {
@@ -115,6 +120,11 @@ int main() {
       std::cout << pwfs_forward(g_plan, &dummy, nf, &dummy, nullptr);
       for (const std::string& s : g_seen) std::cout << ' ' << s;
       std::cout << std::endl;
+    } else if (cmd == "scratch") {
+      int i = 0;
+      long long delta = 0;
+      in >> i >> delta;
+      std::cout << (g_plan->s[i].rbuf_bytes += delta) << std::endl;
     } else if (cmd == "free") {
       pwfs_destroy(g_plan);
       g_plan = nullptr;

@@ -58,6 +58,10 @@ class Host:
             out.append((f[0], int(f[1]), *(int(v) for v in f[2:4])) if len(f) > 2 else (f[0], int(f[1]), None, None))
         return int(rc), out
 
+    def scratch(self, sensor, delta=0):
+        """Recorded bytes of a sensor's scratch, after a change of the record."""
+        return int(self._ask(f"scratch {sensor} {delta}")[0])
+
     def free(self):
         self._ask("free")
 

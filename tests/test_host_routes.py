@@ -56,3 +56,39 @@ def test_pass_sizes_of_saved_tunings_stay_accepted(host, i):
         assert rows and all(x[3] == 0 for x in rows)
     finally:
         host.free()
+
+
+PWFS_EWORKSPACE = -3
+
+
+@pytest.mark.parametrize("s", [_sensor(160, 512, 192, 48), _sensor(64, 128, 64, 16), _sensor(30, 64, 34, 7, nl=2),
+                               _sensor(160, 512, 192, 48, flags=FLAG_DOUBLE_ROOF), _sensor(256, 768, 384, 7, nl=3),
+                               _sensor(96, 256, 120, 16, rings=1, flags=FLAG_REF_SLOPES)],
+                         ids=["160", "64", "30", "roof", "256", "source"])
+def test_every_pass_stays_in_its_scratch_and_a_smaller_one_is_refused(host, s):
+    """Row output and unit sums of every pass size end inside the sensor's scratch
+    (with few frames the sums lie behind them); a scratch that does not hold them
+    is refused before anything is launched."""
+    frames = 48
+    assert host.plan([s], frames)[0] == 0
+    try:
+        parts = set()
+        for nf in range(1, frames + 1):
+            rc, launches = host.forward(nf)
+            assert rc == 0
+            passes = [x for x in launches if x[0] in ("k_toep_rows", "k_toep_cols")]
+            assert passes and all(x[3] == 0 for x in passes), (nf, passes)
+            parts |= {x[2] > 1 for x in passes if x[0] == "k_toep_cols"}
+        assert True in parts
+        size, seen = host.scratch(0), set()
+        for k in range(41):
+            host.scratch(0, size * k // 40 - host.scratch(0))
+            for nf in (1, frames):
+                rc, launches = host.forward(nf)
+                seen.add(rc)
+                assert all(not x[3] for x in launches)
+                if rc and not s.flags & FLAG_DOUBLE_ROOF:      # a roof's first arm may fit where its second does not
+                    assert not launches
+        assert seen == {0, PWFS_EWORKSPACE}
+    finally:
+        host.free()
