@@ -193,12 +193,13 @@ int pwfs_slopes(pwfs_plan_t plan, const float* d_intensity, int n_frames, float*
 
 /*
  * Execution tuning of a plan (chosen by the autotuner, see autotune.py).
- *  mode       PWFS_MODE_LAUNCHES: per sensor, a field, a row and a column
- *             launch per pass; PWFS_MODE_PERSISTENT: one persistent launch per
- *             pass for all Toeplitz sensors and one for all FFT ones, whose
- *             workgroups claim field, row and
- *             column work items from a device counter (a sensor's row items
- *             wait for its field items, its column items for its row items).
+ *  mode       PWFS_MODE_LAUNCHES: per sensor and pass, a row and a column
+ *             launch, before them a field launch (FFT sensors) and behind them
+ *             a sum (Toeplitz sensors, few frames); PWFS_MODE_PERSISTENT: one
+ *             persistent launch per pass for all Toeplitz sensors and one for
+ *             all FFT ones, whose workgroups claim work items from a device
+ *             counter (a sensor's row items wait for its field items, where it
+ *             has them, its column items for its row items).
  *             Both modes give bit-identical results.  PWFS_MODE_FUSED (FP32
  *             pyramid sensors with N = 64 or 128): one launch for all frames,
  *             one workgroup per frame holding the field, the row-pass output
@@ -208,7 +209,8 @@ int pwfs_slopes(pwfs_plan_t plan, const float* d_intensity, int n_frames, float*
  *  chunk      frames per pass, 1 .. max_chunk; fewer where the workspace's
  *             scratch holds fewer
  *  wg_per_cu  persistent workgroups per compute unit, 1 .. 8
- *  row_groups minimum number of row-pass work items per pass
+ *  row_groups minimum number of row-pass work items of a sensor in a
+ *             persistent pass (the launches have their own)
  *  spin_limit polls of a persistent pass's dependency wait before it gives
  *             up (0 = the default, 2^24); a wait that gives up skips its
  *             work item and sets the plan's sticky error flag (pwfs_device_status).
@@ -234,7 +236,9 @@ int pwfs_set_tuning(pwfs_plan_t plan, const pwfs_tuning* tuning);
  * results, in both launch modes.  rows = 0 restores the default.
  * PWFS_EINVAL for a sensor out of range, a tile not compiled for the
  * sensor's N or one whose LDS would exceed 160 KiB; PWFS_EUNSUPPORTED for a
- * sensor that is not on the FP32 path.  Takes effect at the next forward
+ * sensor that is not on the FP32 path.  A sensor that runs as a Toeplitz
+ * product (see pwfs_precision) has no such tile: a selection is accepted and
+ * reported as for any FP32 sensor, and changes nothing.  Takes effect at the next forward
  * call; not to be called while a call on the plan is being enqueued.
  */
 int pwfs_set_row_tile(pwfs_plan_t plan, int sensor, int rows);

@@ -2,12 +2,13 @@
 events.  Two stages:
 
 1. schedule: the launch mode (per-sensor launches or one persistent launch
-   for all sensors), frames per pass, persistent workgroups per CU and the
-   row-pass split, every sensor at its default tile;
+   for all sensors), frames per pass and persistent workgroups per CU, every
+   sensor at its default tile;
 2. tile shapes: for the best schedule of each mode, the row-pass tile (rows
    of the field per workgroup) of each group of sensors with the same FFT
    size, tried in turn and kept where it is faster (a greedy pass: the
-   groups are few and nearly independent).
+   groups are few and nearly independent).  Sensors whose row pass has no
+   such tile (the Toeplitz form) are left out: every tile is the same launch.
 
 The winner is cached in a JSON file keyed by (GPU architecture, sensors,
 frames per call).  Candidates only change how the same arithmetic is
@@ -36,8 +37,8 @@ def candidates(plan) -> List[dict]:
     chunks = sorted({mc, max(1, mc // 2), max(1, mc // 4)}, reverse=True)
     out = []
     for c in chunks:
-        for rg in (1024, 2048, 4096):
-            out.append({"mode": P.MODE_LAUNCHES, "chunk": c, "wg_per_cu": t["wg_per_cu"], "row_groups": rg})
+        # wg_per_cu and row_groups shape the persistent pass only
+        out.append({"mode": P.MODE_LAUNCHES, "chunk": c, "wg_per_cu": t["wg_per_cu"], "row_groups": t["row_groups"]})
     persistent_ok = True
     try:
         plan.set_tuning(mode=P.MODE_PERSISTENT)
@@ -55,10 +56,12 @@ ROW_TILES = (8, 16, 32)   # tried per FFT size; the library accepts the ones com
 
 
 def tile_groups(plan) -> Dict[int, List[int]]:
-    """Sensors grouped by FFT size (the row tiles compiled depend on it)."""
+    """Sensors with a row tile, grouped by FFT size (the tiles compiled depend on it)."""
     groups: Dict[int, List[int]] = {}
+    takes = getattr(plan, "takes_row_tile", lambda i: True)
     for i, s in enumerate(plan.sensors):
-        groups.setdefault(int(s.n_fft), []).append(i)
+        if takes(i):
+            groups.setdefault(int(s.n_fft), []).append(i)
     return groups
 
 

@@ -232,6 +232,13 @@ def validate(sensors) -> int:
     return lib().pwfs_validate(arr, len(arr))
 
 
+def takes_row_tile(s) -> bool:
+    """Whether a sensor's row pass has a tile (pwfs_set_row_tile): the FP32 FFT
+    passes, which run full planes, field stops and pupils above 256 pixels."""
+    d = s if isinstance(s, CSensorDesc) else to_c(s)
+    return d.precision == FP32 and (bool(d.flags & F_FULL_PLANE) or d.fov_lod > 0.0 or d.n_pupil > 256)
+
+
 def workspace_size(sensors, max_frames: int) -> int:
     arr = _descs(sensors)
     n = ctypes.c_size_t()
@@ -395,6 +402,10 @@ class Plan:
         r = ctypes.c_int32()
         check(lib().pwfs_get_row_tile(self._h, int(sensor), ctypes.byref(r)))
         return r.value
+
+    def takes_row_tile(self, sensor: int) -> bool:
+        """Whether the row tile of ``sensor`` changes what it runs."""
+        return takes_row_tile(self.sensors[sensor])
 
     def set_row_tile(self, sensor: int, rows: int) -> None:
         """Selects the row-pass tile of one FP32 sensor (0 = its default; pwfs_set_row_tile)."""
