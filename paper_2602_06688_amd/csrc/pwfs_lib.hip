@@ -215,13 +215,13 @@ Geometry geometry(const pwfs_sensor_desc& d) {
   g.Nc = g.full ? g.N : 2 * g.D;
   g.Dp = (g.D + 15) & ~15;
   g.n_lam = d.n_lambda;
-  {
-    std::vector<TiltPoint> pts;
-    std::vector<double> key_tx;
-    tilt_points(d, pts, key_tx);
-    g.n_mod = (int)pts.size();
-    g.n_a = (int)key_tx.size();
-  }
+  // what tilt_points lists: point k and source point j of ring q; k and n - k, j
+  // and 6 q - j share a key (counted, because the layout asks for a geometry
+  // dozens of times a plan: listing and sorting 1000 points each time took
+  // 2.5 ms of planning)
+  const int R = d.src_rings;
+  g.n_mod = d.n_mod * (1 + 3 * R * (R + 1));
+  g.n_a = (d.n_mod / 2 + 1) * (1 + R + 3 * R * (R + 1) / 2);
   const int stride0 = g.N / fft_r0(g.N);   // distance between the inputs of a first-stage butterfly
   g.qmax = (g.D + stride0 - 1) / stride0;
   return g;
@@ -479,22 +479,24 @@ int upload_tables(const pwfs_sensor_desc& d, char* ws, const size_t* off, hipStr
     }
   }
   for (int i = 0; fft && i < g.N; ++i) put_c(tw, i, cis(-2.0 * kPi * i / g.N));
-  auto up = [&](int region, const void* src, size_t bytes) -> int {
-    if (!bytes) return PWFS_OK;
-    keep.emplace_back((const char*)src, (const char*)src + bytes);
-    HIP_TRY(hipMemcpyAsync(ws + off[region], keep.back().data(), bytes, hipMemcpyHostToDevice, st),
-            "hipMemcpyAsync(tables)");
-    return PWFS_OK;
+  // R_AMP .. R_VALID lie side by side: one copy (eight of 5 to 10 us each were a
+  // third of a small sensor's planning)
+  keep.emplace_back(off[R_VALID] - off[R_AMP] + V.size());
+  char* tab = keep.back().data();
+  auto put = [&](int region, const void* src, size_t bytes) {
+    if (bytes) std::memcpy(tab + (off[region] - off[R_AMP]), src, bytes);
   };
+  put(R_AMP, A.data(), A.size() * sizeof(float));
+  put(R_RX, rx.data(), rx.size() * sizeof(float));
+  put(R_RY, ry.data(), ry.size() * sizeof(float));
+  put(R_AK, ak.data(), ak.size() * sizeof(int));
+  put(R_MROW, mrow.data(), mrow.size() * sizeof(float));
+  put(R_MCOL, mcol.data(), mcol.size() * sizeof(float));
+  put(R_TW, tw.data(), tw.size() * sizeof(float));
+  put(R_VALID, V.data(), V.size());
+  HIP_TRY(hipMemcpyAsync(ws + off[R_AMP], tab, keep.back().size(), hipMemcpyHostToDevice, st),
+          "hipMemcpyAsync(tables)");
   int rc;
-  if ((rc = up(R_AMP, A.data(), A.size() * sizeof(float)))) return rc;
-  if ((rc = up(R_RX, rx.data(), rx.size() * sizeof(float)))) return rc;
-  if ((rc = up(R_RY, ry.data(), ry.size() * sizeof(float)))) return rc;
-  if ((rc = up(R_AK, ak.data(), ak.size() * sizeof(int)))) return rc;
-  if ((rc = up(R_MROW, mrow.data(), mrow.size() * sizeof(float)))) return rc;
-  if ((rc = up(R_MCOL, mcol.data(), mcol.size() * sizeof(float)))) return rc;
-  if ((rc = up(R_TW, tw.data(), tw.size() * sizeof(float)))) return rc;
-  if ((rc = up(R_VALID, V.data(), V.size()))) return rc;
   if (d.flags & PWFS_F_REF_SLOPES) {
     HIP_TRY(hipMemsetAsync(ws + off[R_ZERO], 0, sizeof(float) * g.D * g.D, st), "hipMemsetAsync(zero)");
   }

@@ -302,7 +302,11 @@ int upload_toep_tables(const pwfs_sensor_desc& d, char* dst, hipStream_t st, std
   const Geometry g = geometry(d);
   const int LC = toep_copy_len(t.KS), tl = toep_table_len(t.KS), rl = toep_r_len(t.KS);
   auto c = [&](int n) { return 1.0 / (g.N * std::sin(kPiT * n / g.N)); };
-  std::vector<char> tab(ta256(sizeof(uint16_t) * 2 * tl), 0);
+  // the kernels, the rows' factors, the columns' factors: one copy
+  const size_t rx_at = ta256(sizeof(uint16_t) * 2 * tl),
+               ry_at = rx_at + ta256(sizeof(float) * 2 * rl * (size_t)g.n_lam * g.n_a);
+  keep.emplace_back(toep_table_bytes(d), 0);
+  std::vector<char>& tab = keep.back();
   uint16_t* A = (uint16_t*)tab.data();
   for (int p = 0; p < 2; ++p)
     for (int w = 0; w < 2; ++w)
@@ -327,13 +331,13 @@ int upload_toep_tables(const pwfs_sensor_desc& d, char* dst, hipStream_t st, std
   // factors of one point: register 2 s + j2 = i, lane half h, lane n of 16:
   // sample 8 i + 4 h + (n >> 1 & 3) of parity 1 - p (n < 8) or p, part n & 1
   std::vector<std::complex<double>> z(g.D);
-  auto fill = [&](std::vector<char>& out, size_t at, double tilt, double sc, double sb, double scc) {
+  auto fill = [&](size_t region, size_t at, double tilt, double sc, double sb, double scc) {
     for (int x = g.D / 2; x < g.D; ++x) {
       z[x] = std::polar(1.0, 2.0 * kPiT * sc * tilt * (x - (g.D - 1) / 2.0) / g.D);
       z[g.D - 1 - x] = std::conj(z[x]);
     }
     for (int x = 1; x < g.D; x += 2) z[x] = {-z[x].imag(), z[x].real()};   // odd samples enter times i
-    float* R = (float*)out.data() + at;
+    float* R = (float*)(tab.data() + region) + at;
     for (int p = 0; p < 2; ++p)
       for (int jq = 0; jq < t.Dh; ++jq) {
         float* r = R + (size_t)p * rl + (((jq >> 5) * 2 + (jq >> 2 & 1)) * 16 + 2 * (jq & 3)) * 4 + (jq >> 3 & 3);
@@ -344,26 +348,18 @@ int upload_toep_tables(const pwfs_sensor_desc& d, char* dst, hipStream_t st, std
         r[36] = (float)w.imag();
       }
   };
-  std::vector<char> rx(ta256(sizeof(float) * 2 * rl * (size_t)g.n_lam * g.n_a), 0);
-  std::vector<char> ry(ta256(sizeof(float) * 2 * rl * (size_t)g.n_lam * g.n_mod), 0);
   const double up = std::ldexp(1.0, kToepZExp + kToepKExp);
   for (int l = 0; l < g.n_lam; ++l) {
     const double sc = d.lambda_ref_nm / d.lambda_nm[l];
     const double amp = std::sqrt(d.lambda_weight[l] / wmax);
     for (int a = 0; a < g.n_a; ++a)
-      fill(rx, ((size_t)l * g.n_a + a) * 2 * rl, key_tx[a], sc, std::ldexp(1.0, kToepZExp), 0.5 * up);
+      fill(rx_at, ((size_t)l * g.n_a + a) * 2 * rl, key_tx[a], sc, std::ldexp(1.0, kToepZExp), 0.5 * up);
     for (int k = 0; k < g.n_mod; ++k)
-      fill(ry, ((size_t)l * g.n_mod + k) * 2 * rl, pts[k].ty, sc, amp * std::ldexp(1.0, -kToepKExp), 0.5 * amp);
+      fill(ry_at, ((size_t)l * g.n_mod + k) * 2 * rl, pts[k].ty, sc, amp * std::ldexp(1.0, -kToepKExp), 0.5 * amp);
   }
-  for (std::vector<char>* v : {&tab, &rx, &ry}) {
-    const size_t bytes = v->size();
-    keep.push_back(std::move(*v));
-    const hipError_t e = hipMemcpyAsync(dst, keep.back().data(), bytes, hipMemcpyHostToDevice, st);
-    if (e != hipSuccess) {
-      set_last_error("hipMemcpyAsync(Toeplitz tables)");
-      return PWFS_EHIP;
-    }
-    dst += bytes;
+  if (hipMemcpyAsync(dst, tab.data(), tab.size(), hipMemcpyHostToDevice, st) != hipSuccess) {
+    set_last_error("hipMemcpyAsync(Toeplitz tables)");
+    return PWFS_EHIP;
   }
   return PWFS_OK;
 }

@@ -12,6 +12,7 @@
 //   tune <mode> <chunk> <row_groups>               -> rc max_chunk chunk
 //   fwd <frames>                                   -> rc launch ...
 //   scratch <sensor> <delta>                       -> bytes (its recorded size, changed by delta)
+//   points                                         -> points keys, as counted and as listed, per sensor
 //   free                                           -> 0
 // A launch is kernel:workgroups[:parts:over], parts the workgroups that share a
 // pair of column blocks, over the bytes past the end of the scratch.
@@ -125,6 +126,15 @@ int main() {
       long long delta = 0;
       in >> i >> delta;
       std::cout << (g_plan->s[i].rbuf_bytes += delta) << std::endl;
+    } else if (cmd == "points") {
+      for (const pwfs::SensorPlan& s : g_plan->s) {
+        const pwfs::Geometry g = pwfs::geometry(s.desc);
+        std::vector<pwfs::TiltPoint> pts;
+        std::vector<double> keys;
+        pwfs::tilt_points(s.desc, pts, keys);
+        std::cout << g.n_mod << ' ' << g.n_a << ' ' << pts.size() << ' ' << keys.size() << ' ';
+      }
+      std::cout << std::endl;
     } else if (cmd == "free") {
       pwfs_destroy(g_plan);
       g_plan = nullptr;

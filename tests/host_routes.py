@@ -62,6 +62,10 @@ class Host:
         """Recorded bytes of a sensor's scratch, after a change of the record."""
         return int(self._ask(f"scratch {sensor} {delta}")[0])
 
+    def points(self):
+        """Points and x-tilts of the plan's sensors, counted and listed."""
+        return [int(v) for v in self._ask("points")]
+
     def free(self):
         self._ask("free")
 

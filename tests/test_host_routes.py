@@ -1,6 +1,8 @@
 """Which launches a plan makes, and that they stay inside its scratch: host code
 of the built library alone (tests/host_routes.py), no GPU."""
 
+import time
+
 import pytest
 
 import host_routes
@@ -92,3 +94,27 @@ def test_every_pass_stays_in_its_scratch_and_a_smaller_one_is_refused(host, s):
         assert seen == {0, PWFS_EWORKSPACE}
     finally:
         host.free()
+
+
+@pytest.mark.parametrize("rings", [0, 1, 2, 8])
+@pytest.mark.parametrize("n_mod", [1, 2, 3, 4, 15, 16])
+def test_points_are_counted_as_they_are_listed(host, n_mod, rings):
+    assert host.plan([_sensor(20, 64, 20, n_mod, rings=rings)], 1)[0] == 0
+    n_pts, n_keys, pts, keys = host.points()
+    host.free()
+    assert (n_pts, n_keys) == (pts, keys)
+
+
+def test_sizing_a_plan_does_not_list_its_points():
+    """The layout needs the numbers of points and x-tilts dozens of times: sizing
+    4096 points took 8.7 ms where each was a sorted list, 8 us for 4."""
+    from paper_2602_06688_amd import pwfs as P
+
+    def best(s):
+        ts = []
+        for _ in range(7):
+            t = time.perf_counter()
+            P.workspace_size([s], 1)
+            ts.append(time.perf_counter() - t)
+        return min(ts)
+    assert best(_sensor(20, 64, 20, 4096)) < 10 * best(_sensor(20, 64, 20, 4))
