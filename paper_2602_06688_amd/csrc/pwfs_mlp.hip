@@ -661,20 +661,27 @@ int gemm_ws_launch(const GemmArgs& a0, hipStream_t st) {
 // the wave-specialised ones are 1 % faster).
 constexpr int kWsMinTiles = 512, kWsWideTiles = 1024, kSharedMinTiles = 1024;
 
-// Products of fewer 128 x 128 tiles than two rounds of the chip take 64 x 64
-// tiles (training products of 64 to 200 tiles: 64 us -> 25 to 36 us).  Two-plane
-// products do three times the work per load and only gain while tiles leave CUs
-// idle (400 x 7596 x 576, 240 tiles: 38 us in 128-tiles, 44 us in 64-tiles).
+// Products of few 128 x 128 tiles take 64 x 64 tiles, which reach all CUs and move
+// twice the operand bytes per product.  Plain stores and predictions do up to 320
+// tiles (1000 x 3072 x 1000, 192 tiles: 28 us -> 26; 1000 x 5120 x 1000, 320: 33
+// either way; 3000 x 2600 x 1000, 504: 36 -> 44; 2048 x 3584 x 2000, 448: 57 ->
+// 84), the epilogues of a training step up to two rounds of the chip: their reads
+// and stores run beside the products of the other tiles on a CU (a step of 5120
+// samples, 500-1024-1024-64, hidden layers of 320 tiles: 258 us; in 128-tiles
+// 320).  Two-plane products do three times the work per load and only gain while
+// tiles leave CUs idle (1000 x 3072 x 256, 192 tiles: 0.98; 400 x 7596 x 576, 240
+// tiles: 38 us in 128-tiles, 44 us in 64-tiles).
+template <int EPI>
 bool small_tiles(int planes, int M, int N) {
   const long long tiles = (long long)((M + kGemmTile - 1) / kGemmTile) * ((N + kGemmTile - 1) / kGemmTile);
-  return tiles < (planes == 2 ? 192 : 512);
+  return tiles < (planes == 2 ? 192 : EPI == E_STORE || EPI == E_PREDICT ? 320 : 512);
 }
 
 template <int EPI>
 int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
   if constexpr (EPI == E_OUTPUT)
     if (!a.target) return gemm_dispatch<E_PREDICT>(planes, a, st);
-  if (small_tiles(planes, a.M, a.N)) {
+  if (small_tiles<EPI>(planes, a.M, a.N)) {
     if (planes == 2) return gemm_small_launch<2, EPI, 32>(a, st);
     if (a.K % 64 != 0 || a.K2 % 64 != 0) return gemm_small_launch<1, EPI, 32>(a, st);
     return gemm_small_launch<1, EPI, 64>(a, st);
@@ -1220,7 +1227,7 @@ extern "C" int pwfs_mlp_grad(pwfs_mlp_t m, const float* x, const float* t, int b
   const int L = m->L, pl = m->planes;
   int rc = mlp_forward(m, x, batch, m->Y, 1.f, t, tscale, st);
   if (rc) return rc;
-  const int tile = small_tiles(pl, batch, m->n[L]) ? kSmallTile : kGemmTile;
+  const int tile = small_tiles<E_OUTPUT>(pl, batch, m->n[L]) ? kSmallTile : kGemmTile;
   const int tiles = ((batch + tile - 1) / tile) * ((m->n[L] + tile - 1) / tile);
   if (loss) {
     hipLaunchKernelGGL(k_loss_reduce, dim3(1), dim3(64), 0, st, m->loss_part, tiles,
