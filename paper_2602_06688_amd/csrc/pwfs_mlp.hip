@@ -656,9 +656,10 @@ int gemm_ws_launch(const GemmArgs& a0, hipStream_t st) {
 // else 128 x 128.  The rest (two-plane products, the loss and gradient
 // epilogues) take the 256-lane tiles, and so do hidden layers of at least two
 // rounds of them (two workgroups share a CU): the GELU of one (43 us of vector
-// issue for 20000 x 1024) runs beside the products of the other (a prediction of
-// 20000 samples: 440 us, 451 us wave-specialised; with 664 tiles, 1.3 rounds,
-// the wave-specialised ones are 1 % faster).
+// issue for 20000 x 1024) runs beside the products of the other.  Predictions of a
+// 500-h-h-3200 network, 256-lane and wave-specialised hidden layers: 20000
+// samples, h = 1024: 440 and 451 us; h = 2048: 711 and 737; 32768, h = 1024: 562
+// and 577.  With 664 tiles, 1.3 rounds, the wave-specialised ones are 1 % faster.
 constexpr int kWsMinTiles = 512, kWsWideTiles = 1024, kSharedMinTiles = 1024;
 
 // Products of few 128 x 128 tiles take 64 x 64 tiles, which reach all CUs and move
@@ -689,10 +690,11 @@ int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
   if (planes == 2) return gemm_launch<2, EPI, 32>(a, st);
   if (a.K % 64 != 0 || a.K2 % 64 != 0) return gemm_launch<1, EPI, 32>(a, st);
   if constexpr (EPI != E_DHIDDEN && EPI != E_OUTPUT) {
-    const long long mt = (a.M + kGemmTile - 1) / kGemmTile;
-    if (mt * ((a.N + 255) / 256) >= kWsWideTiles) return gemm_ws_launch<EPI, 256>(a, st);
-    const long long tiles = mt * ((a.N + 127) / 128);
-    if (tiles >= kWsMinTiles && !(EPI == E_HIDDEN && tiles >= kSharedMinTiles)) return gemm_ws_launch<EPI, 128>(a, st);
+    const long long mt = (a.M + kGemmTile - 1) / kGemmTile, tiles = mt * ((a.N + 127) / 128);
+    if (!(EPI == E_HIDDEN && tiles >= kSharedMinTiles)) {
+      if (mt * ((a.N + 255) / 256) >= kWsWideTiles) return gemm_ws_launch<EPI, 256>(a, st);
+      if (tiles >= kWsMinTiles) return gemm_ws_launch<EPI, 128>(a, st);
+    }
   }
   return gemm_launch<1, EPI, 64>(a, st);
 }
