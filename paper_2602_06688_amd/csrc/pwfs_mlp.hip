@@ -52,6 +52,7 @@ struct GemmArgs {
   const uint16_t* b;
   long long a_plane, b_plane, lda, ldb;
   int M, N, K, mtiles, ntiles;
+  int by_row;             // tile order (row_order)
   float alpha, beta;      // E_STORE: c = alpha * acc + beta * c (c is not read when beta == 0)
   float* c;               // fp32 output [M][ldc] (E_STORE, E_OUTPUT)
   long long ldc;
@@ -188,9 +189,16 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, int n, Row row,
 
 // Tile of a workgroup.  Workgroups are dealt to the 8 XCDs in turn: each XCD gets
 // a contiguous eighth of the tiles, in columns of kTileRows row tiles, so that
-// the tiles it runs together share their operand rows in its L2.
+// the tiles it runs together share their operand rows in its L2.  by_row: row by
+// row instead, so that the tiles that run together write whole rows of the output.
 constexpr int kTileRows = 4;
-__device__ __forceinline__ void tile_of(int b, int mtiles, int ntiles, int& mt, int& nt) {
+__device__ __forceinline__ void tile_of(const GemmArgs& p, int b, int& mt, int& nt) {
+  const int mtiles = p.mtiles, ntiles = p.ntiles;
+  if (p.by_row) {
+    mt = b / ntiles;
+    nt = b - mt * ntiles;
+    return;
+  }
   const int total = mtiles * ntiles, q = total >> 3, r = total & 7, x = b & 7;
   const int i = x * q + min(x, r) + (b >> 3);
   const int band = i / (kTileRows * ntiles), in = i - band * kTileRows * ntiles;
@@ -219,7 +227,7 @@ __global__ __launch_bounds__(256) void k_gemm(GemmArgs p) {
   using E = MfmaTile<NPL, false, BK>;
   const int tid = threadIdx.x;
   int mt, nt;
-  tile_of(blockIdx.x, p.mtiles, p.ntiles, mt, nt);
+  tile_of(p, blockIdx.x, mt, nt);
   const int m0 = mt * kGemmTile, n0 = nt * kGemmTile;
   typename E::Ops ops;
 #pragma unroll
@@ -269,7 +277,7 @@ __global__ __launch_bounds__(256) void k_gemm_small(GemmArgs p) {
   __shared__ __align__(16) uint16_t lds[2][gemm_small_stage<NPL, BK>()];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wm = wave >> 1, wn = wave & 1;
   int mt, nt;
-  tile_of(blockIdx.x, p.mtiles, p.ntiles, mt, nt);
+  tile_of(p, blockIdx.x, mt, nt);
   const int m0 = mt * kSmallTile, n0 = nt * kSmallTile;
   const int nk1 = p.K / BK, steps = nk1 + p.K2 / BK;
   const int kq = (tid % CPR) * 8;
@@ -354,7 +362,7 @@ __global__ __launch_bounds__(64 * (2 * BN / 64 + 4)) void k_gemm_ws(GemmArgs p) 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int mt, nt;
-  tile_of(blockIdx.x, p.mtiles, p.ntiles, mt, nt);
+  tile_of(p, blockIdx.x, mt, nt);
   const int m0 = mt * kGemmTile, n0 = nt * BN;
   const int nk1 = p.K / BK;
   const int steps = nk1 + p.K2 / BK;
@@ -678,10 +686,19 @@ bool small_tiles(int planes, int M, int N) {
   return tiles < (planes == 2 ? 192 : EPI == E_STORE || EPI == E_PREDICT ? 320 : 512);
 }
 
+// Products whose time is the stores of the output gain nothing from operand rows
+// in an XCD's L2 and lose the whole rows: those of fewer than kTileRows row tiles
+// (x3, 100 x 25600 x 256: 25.8 us by rows, 33 in XCD bands; 300 x 25600 x 256:
+// 40.3, 43.7; 500 x 25600 x 500: 77.4, 76.0) and of one K step (1000 x 25600 x 64:
+// 33.9, 35.9 in one plane; K = 256: 51.1, 49.2).
+int row_order(const GemmArgs& a) { return a.M <= (kTileRows - 1) * kGemmTile || a.K + a.K2 <= 64; }
+
 template <int EPI>
-int gemm_dispatch(int planes, const GemmArgs& a, hipStream_t st) {
+int gemm_dispatch(int planes, const GemmArgs& a0, hipStream_t st) {
   if constexpr (EPI == E_OUTPUT)
-    if (!a.target) return gemm_dispatch<E_PREDICT>(planes, a, st);
+    if (!a0.target) return gemm_dispatch<E_PREDICT>(planes, a0, st);
+  GemmArgs a = a0;
+  a.by_row = row_order(a);
   if (small_tiles<EPI>(planes, a.M, a.N)) {
     if (planes == 2) return gemm_small_launch<2, EPI, 32>(a, st);
     if (a.K % 64 != 0 || a.K2 % 64 != 0) return gemm_small_launch<1, EPI, 32>(a, st);

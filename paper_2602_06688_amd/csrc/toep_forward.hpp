@@ -140,51 +140,59 @@ struct ToepIdentArgs {
   const int2* kord;
   float* out;
   long long out_stride;
-  int nf, D, Dh, Dq, Nc, cblocks, N, n_a, n_lam, n_mod, o, win_lo, win_hi;
+  int D, Dh, Dq, cblocks, N, n_a, n_lam, n_mod, o, win_lo, win_hi;
   float w2[PWFS_MAX_LAMBDA];
 };
 
-// arm y: R[f][lam][a][x][y] = 2^20 E[f][lam][y][x] rx[lam][a][x], one thread per
-// sample (padding included), in the order of the output within a parity of y
+// Both run one thread per sample of a column block, in the block's own order, so
+// that a wavefront's accesses to the row output are one piece of 512 bytes (with
+// the lanes along y, 16 bytes in 512 each).  Sample `i` of a block: its line,
+// row and offset; a workgroup has 256 samples of one block.
+struct ToepSample {
+  int line, yp, yq, off;
+};
+__device__ __forceinline__ ToepSample toep_sample(int i) {
+  const int r = i & 3, n = (i >> 2) & 15, h = (i >> 6) & 1, q = (i >> 7) & 1, g = i >> 8;
+  return {n, q, 8 * g + 4 * h + r, ((2 * g + q) * 2 + h) * 128 + 8 * n + r};
+}
+
+// arm y: R[f][lam][a][x][y] = 2^20 E[f][lam][y][x] rx[lam][a][x] (padding of y
+// included); one window of columns
 __global__ __launch_bounds__(kToepBlock) void k_toep_rows_ident(ToepIdentArgs p) {
-  const long long i = (long long)blockIdx.x * kToepBlock + threadIdx.x;
-  if (i >= (long long)p.nf * p.n_lam * p.n_a * p.D * 2 * p.Dq) return;
-  const int yl = (int)(i % (2 * p.Dq));
-  long long r = i / (2 * p.Dq);
-  const int x = (int)(r % p.D);
-  r /= p.D;
-  const int a = (int)(r % p.n_a);
+  const unsigned parts = p.Dq / 8;
+  unsigned r = blockIdx.x / parts;
+  const ToepSample t = toep_sample((blockIdx.x - r * parts) * kToepBlock + threadIdx.x);
+  const int a = r % p.n_a;
   r /= p.n_a;
-  const int lam = (int)(r % p.n_lam);
-  const long long f = r / p.n_lam;
-  const int yp = yl >= p.Dq ? 1 : 0, yq = yl - yp * p.Dq;
+  const int cb = r % p.cblocks;
+  r /= p.cblocks;
+  const int lam = r % p.n_lam;
+  const size_t fl = r;   // f n_lam + lam
+  const int l = cb * kToepLines + t.line, xp = l >= p.Dq ? 1 : 0, xq = l - xp * p.Dq;
+  if (xq >= p.Dh) return;
   const size_t bf = toep_block_floats(p.Dq);
-  const float* e = p.field + (f * p.n_lam + lam) * (p.Dq / 8) * bf + toep_at(p.Dq, yl, x >> 1, x & 1);
-  const float2 w = p.rx[((long long)lam * p.n_a + a) * p.D + x];
+  const float* e = p.field + fl * (p.Dq / 8) * bf + toep_at(p.Dq, t.yp * p.Dq + t.yq, xq, xp);
+  const float2 w = p.rx[((long long)lam * p.n_a + a) * p.D + 2 * xq + xp];
   const float2 v = cmul(make_float2(e[0], e[4]), w);
   constexpr float up = (float)(1 << (kToepZExp + kToepKExp));
-  const int l = (x & 1) * p.Dq + (x >> 1);
-  float* d = p.rbuf + (((f * p.n_lam + lam) * p.cblocks + (l >> 4)) * p.n_a + a) * bf + toep_at(p.Dq, l & 15, yq, yp);
+  float* d = p.rbuf + ((fl * p.cblocks + cb) * p.n_a + a) * bf + t.off;
   d[0] = up * v.x;
   d[4] = up * v.y;
 }
 
-// arm x: I[f][o + y][X(xc)] = sum_lam w2[lam] sum_points |R[f][lam][key][xc][y]|^2
+// arm x: I[f][o + y][X] = sum_lam w2[lam] sum_points |R[f][lam][key][X][y]|^2
 __global__ __launch_bounds__(kToepBlock) void k_toep_cols_ident(ToepIdentArgs p) {
-  const long long i = (long long)blockIdx.x * kToepBlock + threadIdx.x;
-  if (i >= (long long)p.nf * p.Nc * p.D) return;
-  const int yl = (int)(i % p.D);
-  long long r = i / p.D;
-  const int xc = (int)(r % p.Nc);
-  const long long f = r / p.Nc;
-  const int yp = yl >= p.Dh ? 1 : 0, yq = yl - yp * p.Dh;
+  const unsigned parts = p.Dq / 8;
+  const unsigned r = blockIdx.x / parts;
+  const ToepSample t = toep_sample((blockIdx.x - r * parts) * kToepBlock + threadIdx.x);
+  const int cb = r % p.cblocks;
+  const size_t f = r / p.cblocks;
+  const int l = cb * kToepLines + t.line, half = l / p.Dq, xq = l - half * p.Dq;   // half: window x 2 + parity
+  if (xq >= p.Dh || t.yq >= p.Dh) return;
   const size_t bf = toep_block_floats(p.Dq);
-  const int xw = xc >= p.D ? 1 : 0, x = xc - xw * p.D;
-  const int l = (2 * xw + (x & 1)) * p.Dq + (x >> 1);
-  const size_t at = toep_at(p.Dq, l & 15, yq, yp);
   float acc = 0.f;
   for (int lam = 0; lam < p.n_lam; ++lam) {
-    const float* base = p.rbuf + ((f * p.n_lam + lam) * p.cblocks + (l >> 4)) * p.n_a * bf + at;
+    const float* base = p.rbuf + ((f * p.n_lam + lam) * p.cblocks + cb) * p.n_a * bf + t.off;
     float part = 0.f, val = 0.f;
     int prev = -1;
     for (int k = 0; k < p.n_mod; ++k) {
@@ -198,8 +206,8 @@ __global__ __launch_bounds__(kToepBlock) void k_toep_cols_ident(ToepIdentArgs p)
     }
     acc += p.w2[lam] * part;
   }
-  const int X = window_coord(xc, p.D, p.win_lo, p.win_hi);
-  p.out[f * p.out_stride + (long long)(p.o + 2 * yq + yp) * p.N + X] = acc;
+  const int X = (half >= 2 ? p.win_hi : p.win_lo) + 2 * xq + (half & 1);
+  p.out[f * p.out_stride + (long long)(p.o + 2 * t.yq + t.yp) * p.N + X] = acc;
 }
 
 }  // namespace
@@ -511,11 +519,9 @@ int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, f
     ia.kord = tp.ca.kord;
     ia.out = out;
     ia.out_stride = out_stride;
-    ia.nf = nf;
     ia.D = g.D;
     ia.Dh = t.Dh;
     ia.Dq = t.Dq;
-    ia.Nc = g.Nc;
     ia.cblocks = tp.ca.cblocks;
     ia.N = g.N;
     ia.n_a = g.n_a;
@@ -531,9 +537,8 @@ int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, f
 
   slot = prof->begin(st);
   if (sp.ident == 2) {
-    const long long n = (long long)nf * g.n_lam * g.n_a * g.D * 2 * t.Dq;
-    hipLaunchKernelGGL(k_toep_rows_ident, dim3((unsigned)((n + kToepBlock - 1) / kToepBlock)), dim3(kToepBlock), 0,
-                       st, ia);
+    const unsigned grid = (unsigned)((long long)nf * g.n_lam * tp.ca.cblocks * g.n_a * (t.Dq / 8));
+    hipLaunchKernelGGL(k_toep_rows_ident, dim3(grid), dim3(kToepBlock), 0, st, ia);
     e = hipGetLastError();
   } else {
     e = toep_rows(t.KS, tp.ra, tp.grid_rows, st);
@@ -543,9 +548,8 @@ int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, f
 
   slot = prof->begin(st);
   if (sp.ident == 1) {
-    const long long n = (long long)nf * g.Nc * g.D;
-    hipLaunchKernelGGL(k_toep_cols_ident, dim3((unsigned)((n + kToepBlock - 1) / kToepBlock)), dim3(kToepBlock), 0,
-                       st, ia);
+    const unsigned grid = (unsigned)((long long)nf * tp.ca.cblocks * (t.Dq / 8));
+    hipLaunchKernelGGL(k_toep_cols_ident, dim3(grid), dim3(kToepBlock), 0, st, ia);
     e = hipGetLastError();
   } else {
     e = toep_cols(t.KS, tp.ca, st);

@@ -38,3 +38,21 @@ def test_remainders_on_both_sides_of_the_tile_rule(prec, M, N, K):
     want = A[:M].double() @ B.double().T
     bound = (REL[prec] + (K + 8) * 2.0 ** -24) * (A[:M].abs().double() @ B.abs().double().T)
     assert bool(((part.double() - want).abs() <= bound).all())
+
+
+@pytest.mark.parametrize("prec", ["BF16", "BF16X3"])
+@pytest.mark.parametrize("hidden,batch", [(1030, 100), (1030, 2600), (1030, 8200), (1030, 16000), (2050, 16400)])
+def test_rows_of_a_prediction_do_not_depend_on_its_batch(prec, hidden, batch):
+    """Hidden layers of 9, 189, 585, 1125 and 2193 tiles (64 x 64, 128 x 128
+    wave-specialised, 256-lane) and the output layers behind them give the rows of
+    a batch of 70 their bits."""
+    from paper_2602_06688_amd import pwfs as P
+    g = torch.Generator(device="cuda").manual_seed(hidden + batch)
+    mlp = P.MLP([33, hidden, 600], max_batch=32 * -(-batch // 32), precision=getattr(P, prec))
+    mlp.set_params(torch.randn(mlp.n_params, device="cuda", generator=g) * 0.05)
+    x = torch.randn(batch, 33, device="cuda", generator=g)
+    print(f"[gpu] prediction {prec} hidden {hidden} batch {batch}", flush=True)
+    few = mlp.forward(x[:70].contiguous()).clone()
+    many = mlp.forward(x)
+    torch.cuda.synchronize()
+    assert torch.equal(few, many[:70]) and bool(torch.isfinite(many).all())
