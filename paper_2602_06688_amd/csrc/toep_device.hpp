@@ -168,6 +168,7 @@ struct ToepColArgs {
   int lgroups;             // column blocks of all frames
   int groups, units;       // summation groups per wavelength; units = n_lam x groups
   int per_wg, n_parts;     // split form: units per workgroup, workgroups per pair of blocks
+  int halves;              // half-split form: workgroups per block
   float* part;             // split form: [units][lgroups][2][8 KS][64] unit sums
   float scale;             // 2^-40 share / (n_mod sum A^2)
 };
@@ -294,19 +295,20 @@ struct ToepWave {
     return u32x4_t{lo[0], lo[1], hi[0], hi[1]};
   }
 
-  // All tiles in turn: use(t, e, v) gets element e of tile t's outputs 1/2 z + K z.
+  // Tiles T0 .. T1 - 1 in turn: use(t, e, v) gets element e of tile t's outputs 1/2 z + K z.
   // The K fragments are read kAhead steps before their products and a tile's
   // outputs are used between the next tile's products; the scheduling barriers
   // keep that order (left to itself the compiler reads each fragment right
   // before its product and waits for it, which doubled the time of this phase).
   static constexpr int kAhead = 2, kRing = kAhead + 1;
-  template <class Use>
+  template <int T0 = 0, int T1 = KS, class Use>
   __device__ __forceinline__ void tiles(const uint16_t* tab, int base, int base_s, Use use) const {
+    constexpr int steps = (T1 - T0) * KS;
     u32x4_t ah[kRing], al[kRing];
     f32x16_t acc[2];
     int at = 0;
     auto fetch = [&](int step) {
-      const int t = step / KS, s = step % KS, q = step % kRing;
+      const int t = T0 + step / KS, s = step % KS, q = step % kRing;
       if (s == 0) {
         at = shared(t) ? base_s : base + (win(t, 0) ? WIN : 0) - 32 * tile_in_win(t);
       }
@@ -314,20 +316,20 @@ struct ToepWave {
       al[q] = frag(tab + at + PLANE + 16 * s);
     };
 #pragma unroll
-    for (int step = 0; step < kAhead && step < KS * KS; ++step) fetch(step);
+    for (int step = 0; step < kAhead && step < steps; ++step) fetch(step);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < KS; ++t) {
+    for (int t = T0; t < T1; ++t) {
       f32x16_t& a = acc[t & 1];
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
-        const int step = t * KS + s, q = step % kRing;
-        if (step + kAhead < KS * KS) fetch(step + kAhead);
+        const int step = (t - T0) * KS + s, q = step % kRing;
+        if (step + kAhead < steps) fetch(step + kAhead);
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
           a = MfmaTile<1, true>::mma(m < 2 ? ah[q] : al[q], m == 1 ? bl[s] : bh[s], s + m == 0 ? zt[tile_in_win(t)] : a);
           const int k = s * NM + m;   // product of the tile; the previous tile's outputs are dealt over them
-          if (t > 0) {
+          if (t > T0) {
 #pragma unroll
             for (int e = 16 * k / (KS * NM); e < 16 * (k + 1) / (KS * NM); ++e) use(t - 1, e, acc[(t & 1) ^ 1][e]);
           }
@@ -336,7 +338,7 @@ struct ToepWave {
       }
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) use(KS - 1, e, acc[(KS - 1) & 1][e]);
+    for (int e = 0; e < 16; ++e) use(T1 - 1, e, acc[(T1 - 1) & 1][e]);
   }
 };
 
@@ -449,7 +451,9 @@ __device__ __forceinline__ void toep_rows_body(const ToepRowArgs& p, int bid, un
 // products run, so that its loads find it in L2.  SPLIT (few frames): the units
 // (wavelength, group) of a pair of blocks are spread over workgroups, which
 // write their sums apart; toep_sum_body adds them in the same order, so both
-// forms give the same bits.
+// forms give the same bits.  Half-split (a frame or two): 1 column block x 2
+// parities x 2 halves of the tiles; with one wavefront on a SIMD a point's chain
+// of products is its time, and the halves' second rotation of z costs nothing.
 constexpr int kToepColThreads = 256;
 // waves per SIMD: the sums and z of KS >= 6 take more than half the register file
 __host__ __device__ constexpr int toep_col_waves(int KS) { return KS <= 2 ? 4 : KS <= 5 ? 2 : 1; }
@@ -459,10 +463,10 @@ __host__ __device__ constexpr size_t toep_lds_cols(bool split) {
   return toep_lds_tab<KS>() + (split ? 0 : 4 * sizeof(float) * 8 * KS * 64);
 }
 
-template <int KS, bool SPLIT>
+template <int KS, bool SPLIT, int T0 = 0, int T1 = KS>
 __device__ __forceinline__ void toep_fold(const float (&part)[16 * KS], float* acc, bool first, int c) {
 #pragma unroll
-  for (int i = 0; i < 8 * KS; ++i) {
+  for (int i = 8 * T0; i < 8 * T1; ++i) {
     const float a = part[2 * i] + lane_swap(part[2 * i]);
     const float b = part[2 * i + 1] + lane_swap(part[2 * i + 1]);
     const float v = c ? b : a;
@@ -489,18 +493,13 @@ __device__ __forceinline__ bool toep_out_col(const ToepColArgs& p, int l, int& X
 
 __device__ __forceinline__ int toep_group_lo(int g, int n_mod, int groups) { return g * n_mod / groups; }
 
-template <int KS, bool SPLIT>
-__device__ __forceinline__ void toep_cols_body(const ToepColArgs& p, int bid, unsigned char* smem, int tid) {
+// One wavefront: units u0 .. u1 - 1 of block lg, parity par, tiles T0 .. T1 - 1;
+// s_tab is staged.
+template <int KS, bool SPLIT, int T0 = 0, int T1 = KS>
+__device__ __forceinline__ void toep_cols_wave(const ToepColArgs& p, int lg, int par, int u0, int u1,
+                                               unsigned char* smem, int wave, int lane) {
   using W = ToepWave<KS>;
   uint16_t* s_tab = (uint16_t*)smem;
-  toep_stage<KS>(s_tab, p.atab, tid, kToepColThreads);
-  __syncthreads();
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int par = wave & 1;
-  const int pairs = (p.lgroups + 1) / 2;
-  const int lg = 2 * (SPLIT ? bid % pairs : bid) + (wave >> 1);
-  const int u0 = SPLIT ? bid / pairs * p.per_wg : 0, u1 = SPLIT ? min(u0 + p.per_wg, p.units) : p.units;
-  if (lg >= p.lgroups) return;
   float* s_acc = (float*)(smem + toep_lds_tab<KS>()) + wave * (8 * KS * 64) + lane;
   const int n = lane & 31, h = lane >> 5, c = n & 1;
   const int bf = toep_block_floats(p.Dq);
@@ -544,13 +543,14 @@ __device__ __forceinline__ void toep_cols_body(const ToepColArgs& p, int bid, un
       const float* ahead = blk + nl * lam_stride + (size_t)ka.y * bf;
       const float t0 = ahead[min(tl0, bf - 1)], t1 = ahead[min(tl1, bf - 1)];
       __builtin_amdgcn_s_setprio(2);
-      w.tiles(s_tab, base, base_s,
+      w.template tiles<T0, T1>(
+              s_tab, base, base_s,
               [&](int t, int e, float v) { part[16 * t + e] = __builtin_fmaf(v, v, part[16 * t + e]); });
       __builtin_amdgcn_s_setprio(0);
       __asm__ volatile("" ::"v"(t0), "v"(t1));
     }
     if constexpr (SPLIT) {
-      toep_fold<KS, true>(part, p.part + ((((size_t)u * p.lgroups + lg) * 2 + par) * 8 * KS) * 64 + lane, true, c);
+      toep_fold<KS, true, T0, T1>(part, p.part + ((((size_t)u * p.lgroups + lg) * 2 + par) * 8 * KS) * 64 + lane, true, c);
     } else {
       toep_fold<KS, false>(part, s_acc, u == 0, c);
     }
@@ -567,6 +567,31 @@ __device__ __forceinline__ void toep_cols_body(const ToepColArgs& p, int bid, un
       if (toep_out_row<KS>(p, k, c, h, par, Y)) out[(size_t)Y * p.N] = s_acc[k * 64] * p.scale;
     }
   }
+}
+
+template <int KS, bool SPLIT>
+__device__ __forceinline__ void toep_cols_body(const ToepColArgs& p, int bid, unsigned char* smem, int tid) {
+  toep_stage<KS>((uint16_t*)smem, p.atab, tid, kToepColThreads);
+  __syncthreads();
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int pairs = (p.lgroups + 1) / 2;
+  const int lg = 2 * (SPLIT ? bid % pairs : bid) + (wave >> 1);
+  const int u0 = SPLIT ? bid / pairs * p.per_wg : 0, u1 = SPLIT ? min(u0 + p.per_wg, p.units) : p.units;
+  if (lg >= p.lgroups) return;
+  toep_cols_wave<KS, SPLIT>(p, lg, wave & 1, u0, u1, smem, wave, lane);
+}
+
+template <int KS>
+__device__ __forceinline__ void toep_cols_halves_body(const ToepColArgs& p, int bid, unsigned char* smem, int tid) {
+  toep_stage<KS>((uint16_t*)smem, p.atab, tid, kToepColThreads);
+  __syncthreads();
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lg = bid % p.lgroups, u0 = bid / p.lgroups * p.per_wg, u1 = min(u0 + p.per_wg, p.units);
+  constexpr int mid = (KS + 1) / 2;
+  if (wave < 2)
+    toep_cols_wave<KS, true, 0, mid>(p, lg, wave & 1, u0, u1, smem, wave, lane);
+  else
+    toep_cols_wave<KS, true, mid, KS>(p, lg, wave & 1, u0, u1, smem, wave, lane);
 }
 
 // split form: adds the units of one value of every lane, in order

@@ -51,6 +51,12 @@ __global__ __launch_bounds__(kToepColThreads, toep_col_waves(KS)) void k_toep_co
 }
 
 template <int KS>
+__global__ __launch_bounds__(kToepColThreads, toep_col_waves(KS)) void k_toep_cols_halves(ToepColArgs p) {
+  extern __shared__ __align__(16) unsigned char toep_smem[];
+  toep_cols_halves_body<KS>(p, blockIdx.x, toep_smem, threadIdx.x);
+}
+
+template <int KS>
 __global__ __launch_bounds__(256) void k_toep_sum(ToepColArgs p) {
   toep_sum_body<KS>(p, blockIdx.x, threadIdx.x);
 }
@@ -68,8 +74,12 @@ hipError_t toep_cols1(const ToepColArgs& a, hipStream_t st) {
                        (toep_lds_cols<KS>(false)), st, a);
     return hipGetLastError();
   }
-  hipLaunchKernelGGL((k_toep_cols<KS, true>), dim3(pairs * a.n_parts), dim3(kToepColThreads),
-                     (toep_lds_cols<KS>(true)), st, a);
+  if (a.halves)   // never with one tile
+    hipLaunchKernelGGL((k_toep_cols_halves<(KS > 1 ? KS : 2)>), dim3((unsigned)a.lgroups * a.n_parts), dim3(kToepColThreads),
+                       (toep_lds_cols<KS>(true)), st, a);
+  else
+    hipLaunchKernelGGL((k_toep_cols<KS, true>), dim3(pairs * a.n_parts), dim3(kToepColThreads),
+                       (toep_lds_cols<KS>(true)), st, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_toep_sum<KS>), dim3((unsigned)(a.lgroups * 4 * KS)), dim3(256), 0, st, a);
@@ -104,7 +114,7 @@ hipError_t toep_cols(int KS, const ToepColArgs& a, hipStream_t st) {
 template <int KS>
 void toep_limit1() {
   const void* fns[] = {(const void*)k_toep_rows<KS>, (const void*)k_toep_cols<KS, false>,
-                       (const void*)k_toep_cols<KS, true>};
+                       (const void*)k_toep_cols<KS, true>, (const void*)k_toep_cols_halves<(KS > 1 ? KS : 2)>};
   for (const void* fn : fns)
     if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
       (void)hipGetLastError();
@@ -257,13 +267,18 @@ static size_t toep_part_frame_bytes(const ToepGeom& t, const Geometry& g) {
 // (split in two they took 63 us a pass against 53).  Model, from measured passes
 // of 1 to 32 frames: a point takes 0.55 + 0.075 KS^2 us with one wavefront on a
 // SIMD and 0.12 KS^2 us each where they share it; the split form adds a launch
-// (4 us) and a write and a read of the sums at 4 TB/s.
-static int toep_parts(const ToepGeom& t, const Geometry& g, int nf, int* per_wg) {
+// (4 us) and a write and a read of the sums at 4 TB/s.  A split pass whose
+// workgroups leave half of the CUs idle takes the half-split form, a workgroup per
+// block (one frame of 160 px, the pass: 8 points 13.2 -> 11.9 us, 16 points 13.4 ->
+// 11.7; a call of 240 px and 8 points 60 -> 53); with more, wavefronts share SIMDs
+// and the second rotation of z costs what the halves give.
+static int toep_parts(const ToepGeom& t, const Geometry& g, int nf, int* per_wg, int* halves) {
   const long long pairs = ((long long)nf * toep_cblocks(g, t) + 1) / 2;
   const int groups = toep_groups(g.n_mod, g.n_lam), units = g.n_lam * groups, waves = toep_col_waves(t.KS);
   const size_t bytes = toep_part_frame_bytes(t, g) * (size_t)nf;
   int parts = 1;
   *per_wg = units;
+  *halves = 0;
   if (bytes > ((size_t)256 << 20)) return 1;
   const double k2 = (double)t.KS * t.KS, unit_points = (double)g.n_mod / groups;
   auto cost = [&](long long wgs, int per) {
@@ -281,6 +296,7 @@ static int toep_parts(const ToepGeom& t, const Geometry& g, int nf, int* per_wg)
       *per_wg = per;
     }
   }
+  *halves = t.KS > 1 && parts > 1 && 2 * pairs * parts <= 256;
   return parts;
 }
 
@@ -293,8 +309,8 @@ size_t toep_scratch_bytes(const pwfs_sensor_desc& d, int chunk) {
   for (int a = 0; a < sensor_arms(d); ++a) {
     const Geometry g = sensor_arms(d) == 2 ? arm_geometry(d, a) : geometry(d);
     const size_t frame = toep_part_frame_bytes(t, g);
-    for (int nf = 1, per; nf <= chunk && frame * nf <= ((size_t)256 << 20); ++nf)
-      if (toep_parts(t, g, nf, &per) > 1) most = std::max(most, ta256(scratch * nf) + frame * (size_t)nf);
+    for (int nf = 1, per, halves; nf <= chunk && frame * nf <= ((size_t)256 << 20); ++nf)
+      if (toep_parts(t, g, nf, &per, &halves) > 1) most = std::max(most, ta256(scratch * nf) + frame * (size_t)nf);
   }
   return most;
 }
@@ -496,7 +512,7 @@ int forward_toep(const SensorPlan& sp, const float* opd, long long opd_stride, f
   ToepPass tp = toep_pass(sp, t, opd, opd_stride, out, out_stride, nf, rbuf, 512);
   size_t need = toep_scratch_frame_bytes(sp.desc) * (size_t)nf;
   if (sp.ident != 1) {
-    tp.ca.n_parts = toep_parts(t, g, nf, &tp.ca.per_wg);
+    tp.ca.n_parts = toep_parts(t, g, nf, &tp.ca.per_wg, &tp.ca.halves);
     tp.ca.part = (float*)((char*)rbuf + ta256(need));
     if (tp.ca.n_parts > 1) need = ta256(need) + toep_part_frame_bytes(t, g) * (size_t)nf;
   }

@@ -49,7 +49,7 @@ long long over(const void* base, const void* end) {
   return n > 0 ? n : 0;
 }
 std::string short_name(const std::string& mangled) {
-  for (const char* k : {"k_toep_rows_ident", "k_toep_cols_ident", "k_toep_rows", "k_toep_cols", "k_toep_sum",
+  for (const char* k : {"k_toep_rows_ident", "k_toep_cols_ident", "k_toep_rows", "k_toep_cols_halves", "k_toep_cols", "k_toep_sum",
                         "k_toep_field", "k_toep_hetero", "k_hetero", "k_fused", "k_rows_ident", "k_cols_ident", "k_rows",
                         "k_cols", "k_field", "k_slopes", "k_counter_reset"})
     if (mangled.find(k) != std::string::npos) return k;
@@ -68,7 +68,7 @@ extern "C" hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, voi
     const auto& a = *(const pwfs::ToepRowArgs*)args[0];
     const size_t nf = a.lgroups / (a.Dq / 8);
     s << ":1:" << over(a.rbuf, a.rbuf + nf * a.n_lam * a.n_a * a.cblocks * pwfs::toep_block_floats(a.Dq));
-  } else if (g_plan && name == "k_toep_cols") {
+  } else if (g_plan && (name == "k_toep_cols" || name == "k_toep_cols_halves")) {
     const auto& a = *(const pwfs::ToepColArgs*)args[0];
     const size_t nf = a.lgroups / a.cblocks, KS = (a.Dh + 15) / 16;
     long long o = over(a.rbuf, a.rbuf + nf * a.n_lam * a.n_a * a.cblocks * pwfs::toep_block_floats(a.Dq));

@@ -6,6 +6,7 @@ import time
 import pytest
 
 import host_routes
+from test_gpu_toep_forms import CASES as FORMS, sensor as forms_sensor
 from workloads import FLAG_DOUBLE_ROOF, FLAG_REF_SLOPES, PREC_BF16X3, PREC_FP16X3, PREC_FP32, tiny_sensor
 
 
@@ -54,7 +55,7 @@ def test_pass_sizes_of_saved_tunings_stay_accepted(host, i):
         assert rc == 0 and chunk == accepted
         rc, launches = host.forward(frames)
         assert rc == 0
-        rows = [x for x in launches if x[0] in ("k_toep_rows", "k_toep_cols")]
+        rows = [x for x in launches if x[0] in ("k_toep_rows", "k_toep_cols", "k_toep_cols_halves")]
         assert rows and all(x[3] == 0 for x in rows)
     finally:
         host.free()
@@ -78,9 +79,9 @@ def test_every_pass_stays_in_its_scratch_and_a_smaller_one_is_refused(host, s):
         for nf in range(1, frames + 1):
             rc, launches = host.forward(nf)
             assert rc == 0
-            passes = [x for x in launches if x[0] in ("k_toep_rows", "k_toep_cols")]
+            passes = [x for x in launches if x[0] in ("k_toep_rows", "k_toep_cols", "k_toep_cols_halves")]
             assert passes and all(x[3] == 0 for x in passes), (nf, passes)
-            parts |= {x[2] > 1 for x in passes if x[0] == "k_toep_cols"}
+            parts |= {x[2] > 1 for x in passes if x[0] != "k_toep_rows"}
         assert True in parts
         size, seen = host.scratch(0), set()
         for k in range(41):
@@ -118,3 +119,20 @@ def test_sizing_a_plan_does_not_list_its_points():
             ts.append(time.perf_counter() - t)
         return min(ts)
     assert best(_sensor(20, 64, 20, 4096)) < 10 * best(_sensor(20, 64, 20, 4))
+
+
+@pytest.mark.parametrize("i", range(len(FORMS)))
+def test_frames_of_the_forms_test_take_their_forms(host, i):
+    D, N, sep, n_mod, nl, half, split, whole = FORMS[i]
+    assert host.plan([forms_sensor(D, N, sep, n_mod, nl)], whole)[0] == 0
+    try:
+        for frames, form in ((half, "half"), (split, "split"), (whole, "whole")):
+            if frames:
+                rc, launches = host.forward(frames)
+                (cols,) = [x for x in launches if x[0] in ("k_toep_cols", "k_toep_cols_halves")]
+                sums = [x for x in launches if x[0] == "k_toep_sum"]
+                assert rc == 0 and cols[3] == 0
+                assert (cols[0] == "k_toep_cols_halves", cols[2] > 1, len(sums)) == {
+                    "half": (True, True, 1), "split": (False, True, 1), "whole": (False, False, 0)}[form]
+    finally:
+        host.free()
