@@ -225,14 +225,25 @@ __global__ __launch_bounds__(kToepBlock) void k_toep_cols_ident(ToepIdentArgs p)
 }  // namespace
 
 // ---------------------------------------------------------- eligibility ----
-// Window-mode sensors without a field stop (a stop's kernel is neither real
-// nor sparse) and D <= 256 (the register tiles compiled), in FP32 and the split
-// precisions.  All of these take float16 hi and lo parts: bfloat16 ones, at the
-// same rate, err by 2.6e-6 where the dense DFT products err by 1.3e-6.  The
-// one-term precisions keep their own products, whose rounding is their result.
+// Window-mode sensors without a field stop (the near and the far face of a stop
+// are different kernels, which take twice the products) and D <= 256 (the register
+// tiles compiled), in FP32 and the split precisions.  All of these take float16 hi
+// and lo parts: bfloat16 ones, at the same rate, err by 2.6e-6 where the dense DFT
+// products err by 1.3e-6.  The one-term precisions keep their own products, whose
+// rounding is their result.
+//
+// A line costs KS^2 products here and a pair of N-point transforms there.  The
+// widest tiles against the shortest transforms that hold them, pupils above 224
+// pixels on 512 points, gain nothing from 16 points on (100 frames of 48 points:
+// 226 px 2660 us by FFT, 2920; 242 px 2880, 3390; 256 px 2900, 3150; one frame of
+// 16: 54 and 64) and stay with the FFT passes; with few points (8: 752 and 737 us;
+// 730 and 665) and as double roofs, whose flat axes are copies, they do not.
 bool toep_eligible(const pwfs_sensor_desc& d) {
   if (d.precision == PWFS_FP16 || d.precision == PWFS_BF16) return false;
-  return !(d.flags & PWFS_F_FULL_PLANE) && !(d.fov_lod > 0.0) && d.n_pupil <= 32 * kToepMaxKS;
+  if ((d.flags & PWFS_F_FULL_PLANE) || d.fov_lod > 0.0 || d.n_pupil > 32 * kToepMaxKS) return false;
+  const int points = d.n_mod * (1 + 3 * d.src_rings * (d.src_rings + 1));
+  return !(d.precision == PWFS_FP32 && !(d.flags & PWFS_F_DOUBLE_ROOF) && d.n_pupil > 224 && d.n_fft <= 512 &&
+           points >= 16);
 }
 
 // column blocks per frame and key: windows x 2 parities x Dq lines

@@ -234,9 +234,14 @@ def validate(sensors) -> int:
 
 def takes_row_tile(s) -> bool:
     """Whether a sensor's row pass has a tile (pwfs_set_row_tile): the FP32 FFT
-    passes, which run full planes, field stops and pupils above 256 pixels."""
+    passes, which run full planes, field stops, pupils above 256 pixels, and on
+    512 points pyramids above 224 pixels of at least 16 points."""
     d = s if isinstance(s, CSensorDesc) else to_c(s)
-    return d.precision == FP32 and (bool(d.flags & F_FULL_PLANE) or d.fov_lod > 0.0 or d.n_pupil > 256)
+    if d.precision != FP32:
+        return False
+    points = d.n_mod * (1 + 3 * d.src_rings * (d.src_rings + 1))
+    wide = d.n_pupil > 224 and d.n_fft <= 512 and points >= 16 and not d.flags & F_DOUBLE_ROOF
+    return bool(d.flags & F_FULL_PLANE) or d.fov_lod > 0.0 or d.n_pupil > 256 or wide
 
 
 def workspace_size(sensors, max_frames: int) -> int:

@@ -10,8 +10,8 @@ from test_autotune import FakePlan, _sensor as fake_sensor
 from workloads import FLAG_DOUBLE_ROOF, FLAG_FULL_PLANE, PREC_BF16, PREC_FP16X3, tiny_sensor
 
 
-def _sensor(D, N, **kw):
-    return tiny_sensor(n_pupil=D, n_fft=N, n_subap=D // 4, pupil_sep_px=float(min(N - D, 2 * (D * 3 // 5))), n_mod=8,
+def _sensor(D, N, n_mod=8, **kw):
+    return tiny_sensor(n_pupil=D, n_fft=N, n_subap=D // 4, pupil_sep_px=float(min(N - D, 2 * (D * 3 // 5))), n_mod=n_mod,
                        mod_radius_lod=2.0, **kw)
 
 
@@ -20,6 +20,10 @@ SENSORS = [
     (_sensor(80, 256), False), (_sensor(256, 768), False), (_sensor(258, 768), True), (_sensor(64, 128), False),
     (_sensor(80, 256, fov_lod=30.0), True), (_sensor(80, 256, flags=FLAG_FULL_PLANE), True),
     (_sensor(80, 256, flags=FLAG_DOUBLE_ROOF), False), (_sensor(80, 256, flags=FLAG_DOUBLE_ROOF, fov_lod=30.0), True),
+    (_sensor(226, 512, n_mod=15), False), (_sensor(226, 512, n_mod=16), True), (_sensor(224, 512, n_mod=48), False),
+    (_sensor(256, 512, n_mod=3, src_rings=1, src_radius_lod=1.0), True), (_sensor(256, 768, n_mod=48), False),
+    (_sensor(226, 512, n_mod=48, flags=FLAG_DOUBLE_ROOF), False),
+    (_sensor(226, 512, n_mod=48, precision=PREC_FP16X3), False),
     (_sensor(80, 256, precision=PREC_FP16X3), False), (_sensor(80, 256, precision=PREC_BF16), False),
 ]
 
