@@ -338,11 +338,14 @@ extern "C" int pwfs_sh_validate(const pwfs_sh_desc* d) {
     if (std::fabs(wsum - 1.0) > 1e-9) return sfail(PWFS_EINVAL, "lambda_weights must sum to 1");
   }
   const int k = d->n_fft / d->rebin;
-  // the size of the unfolded tables, which the folded ones stay below
+  // What is admitted goes by the size of unfolded tables, in at most 150 KiB.  The
+  // folded ones are smaller from b = 4 on and a little larger for b = 1 and 3: at
+  // most 152 KiB of what is admitted (b = 1, n_fft = 382, rebin 2).
   const size_t wide = (size_t)(b % 2 == 0 ? b + 1 : b), tall = (size_t)(d->n_fft <= 256 ? 257 : d->n_fft);
   const size_t lds = sizeof(float2) * ((size_t)d->n_fft * wide + (size_t)b * tall + (size_t)b * b) +
                      sizeof(float) * ((size_t)k * k + kShBlock);
-  if (lds > 150 * 1024) return sfail(PWFS_EUNSUPPORTED, "subaperture tables exceed the LDS (n_fft x b too large)");
+  if (lds > 150 * 1024 || sh_lds(b, d->n_fft, k, kShBlock) > 160 * 1024)
+    return sfail(PWFS_EUNSUPPORTED, "subaperture tables exceed the LDS (n_fft x b too large)");
   return PWFS_OK;
 }
 
