@@ -21,9 +21,11 @@
 // Arithmetic.  K and z are split into 16-bit hi and lo parts (x = hi + lo)
 // and K z = Kh zh + Kh zl + Kl zh accumulates in float32; the 1/2 z term, half
 // of the energy, enters the accumulator in full float32.  K and z are scaled
-// by 2^10, so no lo part that matters is a float16 subnormal.  Measured against
-// float64 on the 160 px sensor: 1.3e-7 of the intensity (the float32 FFT pair:
-// 2.5e-7).
+// by 2^10, so no lo part that matters is a float16 subnormal.  Relative rms error
+// against float64, 16 frames of the 160 px sensor: 9.9e-8 of the intensities and
+// 1.85e-7 of the slopes (the float32 FFT pair: 2.5e-7 and 1.84e-7); over 50
+// unmodulated sensors, whose errors no sum over points averages, 1.5e-7 and
+// 1.67e-7 (2.4e-7 and 1.65e-7).
 //
 // Work split.  A wavefront owns 16 lines (rows, or columns) x (re, im) = the 32
 // columns of a 32x32x16 product, and the outputs of one parity p in both
@@ -43,10 +45,14 @@
 //    float32 for the 1/2 z term.
 //  What bounds it.  Rows: the HBM writes of their output (10.2 MB per frame of
 //  the 160 px sensor; 200 frames in 410 us, 5.0 TB/s, a large copy's rate; the FFT
-//  rows took 930 us).  Columns: the chip's power.  Their matrix, vector and load
-//  streams overlap to about 80% of the matrix cores' issue, at which the clock
-//  falls to 1.4 - 1.7 GHz (all-zero data runs 1.4 times faster): 200 frames x 48
-//  points in 1.13 - 1.29 ms against 2.30 ms for the FFT columns.  Measured and slower:
+//  rows took 930 us).  Columns: by the counters the products are busy for 0.50 of
+//  the cycles of a SIMD and the other vector instructions for 0.44; a wavefront
+//  forms a point's z before its products, so that the two fill 0.94 of them
+//  unless the two wavefronts of a SIMD overlap.  The clock falls to 1.4 - 1.7 GHz
+//  (the same launch on zeros is 1.4 times faster); which of the two holds it has
+//  not been told apart.  The products come at 0.8 of the rate of a large bf16
+//  library product: 200 frames x 48 points in 1.08 - 1.29 ms against 2.30 ms for
+//  the FFT columns.  Measured and slower:
 //  blocks through LDS (1440 us), the four waves of a block in step with a
 //  barrier (1345 us), passes small enough for the 256 MB cache (2200 us).
 //  * Accumulator element 4 j + r of a lane is row 8 j + 4 (lane / 32) + r, and
@@ -68,9 +74,12 @@ constexpr int kToepLines = 16;   // lines of one wavefront
 constexpr int kToepMaxKS = 8;    // D <= 256
 // Summation groups of a wavelength's modulation points: up to 16 over all
 // wavelengths, of at least 3 points (few frames spread them over workgroups; a
-// group's end costs a batch about 3% of 3 points).
+// group's end costs a batch about 3% of 3 points).  4 and 5 points make two: one
+// chain is the time of a frame alone (160 px, the call: 32.2 and 34.2 us, in two
+// groups 27.4 and 29.3, FFT passes 27.0 and 28.2; 16 frames 42.6 and 44.7, 44.7
+// and 46.8, FFT 57.8 and 61.7).
 __host__ __device__ inline int toep_groups(int n_mod, int n_lam) {
-  const int most = n_lam < 16 ? 16 / n_lam : 1, g = n_mod / 3;
+  const int most = n_lam < 16 ? 16 / n_lam : 1, g = n_mod >= 4 && n_mod < 6 ? 2 : n_mod / 3;
   return g < 1 ? 1 : g < most ? g : most;
 }
 

@@ -1,6 +1,6 @@
 // toep_forward.hpp -- kernels and host side of the Toeplitz form of the
 // forward model (toep_device.hpp): which sensors take it, its tables and
-// scratch, the pupil field in its layout, and its launches.
+// scratch, the flat axes of double roofs in its layout, and its launches.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -278,11 +278,15 @@ static size_t toep_part_frame_bytes(const ToepGeom& t, const Geometry& g) {
 // (split in two they took 63 us a pass against 53).  Model, from measured passes
 // of 1 to 32 frames: a point takes 0.55 + 0.075 KS^2 us with one wavefront on a
 // SIMD and 0.12 KS^2 us each where they share it; the split form adds a launch
-// (4 us) and a write and a read of the sums at 4 TB/s.  A split pass whose
-// workgroups leave half of the CUs idle takes the half-split form, a workgroup per
-// block (one frame of 160 px, the pass: 8 points 13.2 -> 11.9 us, 16 points 13.4 ->
-// 11.7; a call of 240 px and 8 points 60 -> 53); with more, wavefronts share SIMDs
-// and the second rotation of z costs what the halves give.
+// (4 us) and a write and a read of the sums at 4 TB/s.
+//
+// A split pass whose workgroups leave half of the CUs idle takes the half-split
+// form, a workgroup per block (one frame of 160 px, the pass: 8 points 13.2 -> 11.9
+// us, 16 points 13.4 -> 11.7; a call of 240 px and 8 points 60 -> 53); with more,
+// wavefronts share SIMDs and the second rotation of z costs what the halves give.
+// A whole pass takes it where that is shorter: a point takes 0.55 + 0.06 KS^2 us
+// there and a group's end 0.2 KS us, 0.45 KS in the whole form, which waits for
+// its LDS (one frame of 80 px and 6 points, the call: 23.2 -> 19.9 us).
 static int toep_parts(const ToepGeom& t, const Geometry& g, int nf, int* per_wg, int* halves) {
   const long long pairs = ((long long)nf * toep_cblocks(g, t) + 1) / 2;
   const int groups = toep_groups(g.n_mod, g.n_lam), units = g.n_lam * groups, waves = toep_col_waves(t.KS);
@@ -292,6 +296,7 @@ static int toep_parts(const ToepGeom& t, const Geometry& g, int nf, int* per_wg,
   *halves = 0;
   if (bytes > ((size_t)256 << 20)) return 1;
   const double k2 = (double)t.KS * t.KS, unit_points = (double)g.n_mod / groups;
+  const double extra = 4.0 + 2.0 * (double)bytes / 4e6;
   auto cost = [&](long long wgs, int per) {
     const long long rounds = (wgs + 256 * waves - 1) / (256 * waves);
     const double share = (double)(rounds == 1 ? (wgs + 255) / 256 : waves);
@@ -300,14 +305,30 @@ static int toep_parts(const ToepGeom& t, const Geometry& g, int nf, int* per_wg,
   double best = cost(pairs, units);
   for (int s = 2; s <= units; ++s) {
     const int per = (units + s - 1) / s, n = (units + per - 1) / per;
-    const double c = cost(pairs * n, per) + 4.0 + 2.0 * (double)bytes / 4e6;
+    const double c = cost(pairs * n, per) + extra;
     if (c < best) {
       best = c;
       parts = n;
       *per_wg = per;
     }
   }
-  *halves = t.KS > 1 && parts > 1 && 2 * pairs * parts <= 256;
+  if (t.KS == 1) return parts;
+  auto lone = [&](int n) { return 2 * pairs * n <= 256; };
+  if (parts > 1) {
+    *halves = lone(parts);
+  } else {
+    best += 0.45 * t.KS * units;   // group ends
+    for (int s = 2; s <= units; ++s) {
+      const int per = (units + s - 1) / s, n = (units + per - 1) / per;
+      const double c = per * (unit_points * (0.55 + 0.06 * k2) + 0.2 * t.KS) + extra;
+      if (lone(n) && c < best) {
+        best = c;
+        parts = n;
+        *per_wg = per;
+        *halves = 1;
+      }
+    }
+  }
   return parts;
 }
 
@@ -408,7 +429,7 @@ void toep_prepare() {
 
 namespace {
 
-// Arguments of the three passes of one sensor over nf frames.
+// Arguments of the passes of one sensor over nf frames.
 struct ToepPass {
   ToepRowArgs ra;
   ToepColArgs ca;

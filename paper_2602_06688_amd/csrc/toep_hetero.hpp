@@ -1,7 +1,7 @@
-// toep_hetero.hpp -- persistent pass of a plan's Toeplitz sensors: the field,
-// row and column passes of all of them in one launch, claimed from a device
-// counter like k_hetero's (same counters, dependency waits and error flag).
-// The bodies are those of the per-sensor launches, so both give the same bits.
+// toep_hetero.hpp -- persistent pass of a plan's Toeplitz sensors: the row and
+// column passes of all of them in one launch, claimed from a device counter like
+// k_hetero's (same counters, dependency waits and error flag).  The bodies are
+// those of the per-sensor launches, so both give the same bits.
 // One workgroup of 256 lanes per CU: the largest tiles take the register file
 // of one wave per SIMD.
 #pragma once

@@ -17,8 +17,8 @@ pytestmark = pytest.mark.gpu
 # pupil, grid, separation, points, wavelengths; frames of the half-split, split and whole form (0: not taken)
 CASES = [
     (32, 64, 32, 12, 1, 0, 3, 50), (34, 128, 62, 9, 1, 14, 0, 15), (64, 128, 64, 16, 1, 6, 7, 31),
-    (66, 256, 128, 7, 1, 2, 0, 3), (94, 256, 126, 6, 2, 5, 6, 15), (98, 256, 126, 7, 1, 9, 10, 12),
-    (128, 256, 128, 9, 1, 5, 6, 11), (130, 384, 156, 6, 2, 3, 4, 15), (160, 512, 192, 7, 1, 6, 7, 13),
+    (66, 256, 128, 16, 1, 5, 6, 21), (94, 256, 126, 6, 2, 5, 6, 15), (98, 256, 126, 7, 1, 9, 10, 12),
+    (128, 256, 128, 9, 1, 5, 6, 11), (130, 384, 156, 6, 2, 3, 4, 15), (160, 512, 192, 7, 1, 6, 7, 13), (160, 512, 192, 5, 1, 6, 7, 9),
     (162, 384, 192, 6, 1, 5, 6, 12), (192, 384, 192, 16, 1, 2, 3, 13), (194, 512, 254, 7, 1, 4, 5, 10),
     (222, 512, 254, 6, 2, 2, 3, 10), (226, 768, 384, 6, 1, 4, 5, 9), (256, 768, 384, 7, 1, 4, 5, 9),
 ]
