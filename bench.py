@@ -975,7 +975,7 @@ def main() -> int:
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32",
+        "dtype": "fp16x3 (f32 inputs, sums and outputs)",
         "arithmetic": "float32 operands as fp16 hi and lo parts (22 significand bits), three matrix products, "
                       "float32 sums",
         "data": "synthetic von Karman screens (r0 0.12 m, L0 40 m) + 5 mas tip/tilt jitter, seeds 2/12",
@@ -983,7 +983,7 @@ def main() -> int:
         "host": host,
         "config": {"workload": w.name, "frames_per_step": w.n_frames, "n_pupil": s.n_pupil, "n_fft": s.n_fft,
                    "n_mod": s.n_mod, "n_subap": s.n_subap, "obstruction": s.obstruction,
-                   "lambda_nm": s.lambdas_nm[0], "precision": "fp32", "intensity": "pupil-image windows"},
+                   "lambda_nm": s.lambdas_nm[0], "precision": "fp32 (Toeplitz products in fp16x3)", "intensity": "pupil-image windows"},
         "roofline": matrix_roofline(
             achieved, {"flops_per_frame": flops["cols"]},
             kernel="k_toep_cols (columns as real Toeplitz products on fp16 hi/lo parts, |e|^2 accumulate)",

@@ -45,9 +45,9 @@
 //    float32 for the 1/2 z term.
 //  What bounds it.  Rows: the HBM writes of their output (10.2 MB per frame of
 //  the 160 px sensor; 200 frames in 410 us, 5.0 TB/s, a large copy's rate; the FFT
-//  rows took 930 us).  Columns: by the counters the products are busy for 0.50 of
-//  the cycles of a SIMD and the other vector instructions for 0.44; a wavefront
-//  forms a point's z before its products, so that the two fill 0.94 of them
+//  rows took 930 us).  Columns: by the counters the products are busy for 0.52 of
+//  the cycles of a SIMD and the other vector instructions for 0.45; a wavefront
+//  forms a point's z before its products, so that the two fill 0.97 of them
 //  unless the two wavefronts of a SIMD overlap.  The clock falls to 1.4 - 1.7 GHz
 //  (the same launch on zeros is 1.4 times faster); which of the two holds it has
 //  not been told apart.  The products come at 0.8 of the rate of a large bf16
