@@ -52,7 +52,7 @@ struct GemmArgs {
   const uint16_t* b;
   long long a_plane, b_plane, lda, ldb;
   int M, N, K, mtiles, ntiles;
-  int by_row;             // tile order (row_order)
+  int xcd_bits, band;     // tile order (tile_order)
   float alpha, beta;      // E_STORE: c = alpha * acc + beta * c (c is not read when beta == 0)
   float* c;               // fp32 output [M][ldc] (E_STORE, E_OUTPUT)
   long long ldc;
@@ -188,23 +188,19 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, int n, Row row,
 }
 
 // Tile of a workgroup.  Workgroups are dealt to the 8 XCDs in turn: each XCD gets
-// a contiguous eighth of the tiles, in columns of kTileRows row tiles, so that
-// the tiles it runs together share their operand rows in its L2.  by_row: row by
-// row instead, so that the tiles that run together write whole rows of the output.
+// a contiguous eighth of the tiles, in columns of `band` = kTileRows row tiles, so
+// that the tiles it runs together share their operand rows in its L2.  Row by row
+// (xcd_bits 0, band 1) the tiles that run together write whole rows of the output.
+// Both by the same arithmetic: a branch here cost a prediction 1.2 %.
 constexpr int kTileRows = 4;
 __device__ __forceinline__ void tile_of(const GemmArgs& p, int b, int& mt, int& nt) {
-  const int mtiles = p.mtiles, ntiles = p.ntiles;
-  if (p.by_row) {
-    mt = b / ntiles;
-    nt = b - mt * ntiles;
-    return;
-  }
-  const int total = mtiles * ntiles, q = total >> 3, r = total & 7, x = b & 7;
-  const int i = x * q + min(x, r) + (b >> 3);
-  const int band = i / (kTileRows * ntiles), in = i - band * kTileRows * ntiles;
-  const int rows = min(kTileRows, mtiles - band * kTileRows);
+  const int mtiles = p.mtiles, ntiles = p.ntiles, mask = (1 << p.xcd_bits) - 1;
+  const int total = mtiles * ntiles, q = total >> p.xcd_bits, r = total & mask, x = b & mask;
+  const int i = x * q + min(x, r) + (b >> p.xcd_bits);
+  const int band = i / (p.band * ntiles), in = i - band * p.band * ntiles;
+  const int rows = min(p.band, mtiles - band * p.band);
   nt = in / rows;
-  mt = band * kTileRows + in - nt * rows;
+  mt = band * p.band + in - nt * rows;
 }
 
 // the squared error of a workgroup of 256 lanes
@@ -687,18 +683,24 @@ bool small_tiles(int planes, int M, int N) {
 }
 
 // Products whose time is the stores of the output gain nothing from operand rows
-// in an XCD's L2 and lose the whole rows: those of fewer than kTileRows row tiles
-// (x3, 100 x 25600 x 256: 25.8 us by rows, 33 in XCD bands; 300 x 25600 x 256:
-// 40.3, 43.7; 500 x 25600 x 500: 77.4, 76.0) and of one K step (1000 x 25600 x 64:
-// 33.9, 35.9 in one plane; K = 256: 51.1, 49.2).
-int row_order(const GemmArgs& a) { return a.M <= (kTileRows - 1) * kGemmTile || a.K + a.K2 <= 64; }
+// in an XCD's L2 and lose the whole rows: those of one K step (one plane, 1000 x
+// 25600 x 64: 33.9 us by rows, 35.9 in XCD bands; K = 256: 51.1, 49.2), of one row
+// tile (x3, 100 x 25600 x 256: 25.8, 33) and of two or three, if they are more than
+// a round of the chip (300 x 25600 x 256: 40.3, 43.7; 256 x 12800 x 256, 200 tiles:
+// 26.3, 25.2; four, 500 x 25600 x 500: 77.4, 76.0).
+void tile_order(GemmArgs& a) {
+  const long long mt = (a.M + kGemmTile - 1) / kGemmTile, nt = (a.N + kGemmTile - 1) / kGemmTile;
+  const bool by_row = a.K + a.K2 <= 64 || mt == 1 || (mt < kTileRows && mt * nt > 256);
+  a.xcd_bits = by_row ? 0 : 3;
+  a.band = by_row ? 1 : kTileRows;
+}
 
 template <int EPI>
 int gemm_dispatch(int planes, const GemmArgs& a0, hipStream_t st) {
   if constexpr (EPI == E_OUTPUT)
     if (!a0.target) return gemm_dispatch<E_PREDICT>(planes, a0, st);
   GemmArgs a = a0;
-  a.by_row = row_order(a);
+  tile_order(a);
   if (small_tiles<EPI>(planes, a.M, a.N)) {
     if (planes == 2) return gemm_small_launch<2, EPI, 32>(a, st);
     if (a.K % 64 != 0 || a.K2 % 64 != 0) return gemm_small_launch<1, EPI, 32>(a, st);
